@@ -295,6 +295,8 @@ struct mcs_plan {
     int waves_per_block = 4, blocks = 0, waves = 0, lds_per_block = 0;
     int seg_log = 0;   // 3 or 4: searches of 2^seg_log lanes (mcs_seg.hip); 0: one per wavefront
     int seg_bytes = 0, arows = 0;
+    bool lane = false;  // a search in every lane (mcs_lane.hip)
+    int lane_kc = 0, lane_stride = 0, lane_big = 0;
     double tick_hz = 1e8;
 
     uint8_t *ws = nullptr;
@@ -383,8 +385,10 @@ const char *mcs_status_string(mcs_status s) {
 
 const char *mcs_last_error(void) { return g_err.c_str(); }
 
-mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H,
-                           const mcs_opts *opts, mcs_plan **out) {
+// may_lane: the kernel with a search in every lane may be chosen (the
+// static-scratch entry keeps the kernels whose stacks fit there).
+static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H,
+                              const mcs_opts *opts, mcs_plan **out, bool may_lane) {
     g_err.clear();
     if (!out)
         return fail(MCS_E_INVALID, "out is NULL");
@@ -598,7 +602,26 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
             p->seg_log = 0;
         else
             p->seg_log = sl == 4 ? 2 : sl == 16 ? 4 : 3;  // default: 8 lanes
+        // The default is a search in every lane (mcs_lane.hip), unless a knob
+        // of another kernel is set.  With wide rows only if no instance can
+        // dive deep: a frame of close to n classes is one long loop of a
+        // lane but a few steps of a wavefront, and an instance whose Eq. 1
+        // bound at the root is near its size (unlabelled graphs, relabelled
+        // copies) may have to go through n of them one after another (eight
+        // pairs of a graph of 129 to 254 vertices and its copy: 2.5 ms with a
+        // search per wavefront, 71 ms with one per lane).  Random labelled
+        // pairs have root bounds of about 0.5 to 0.8 of their size and
+        // frames of ten to twenty classes.
+        bool deep = false;
+        for (int i = 0; wide && i < ndev; i++)
+            deep = deep || 8 * p->root_bound[i] > 7 * p->m[i];
+        p->lane = may_lane && sl == 0 && !p->policy && p->tun.stack_classes <= 0 && !deep &&
+                  !(wide && p->tun.children_per_wave > 0);
+        if (p->lane)
+            p->seg_log = 0;
     }
+    const int hdr_e = mcs::lane_hdr_entries(p->word_bytes), entry = 2 * p->word_bytes;
+    const int worst_e = mcs::lane_worst_entries(p->word_bytes, p->mmax);
     const int nseg = p->seg_log ? 64 >> p->seg_log : 1;
     if (p->seg_log) {
         // adjacency rows a segment keeps: the batch's largest graph, to 4
@@ -648,13 +671,24 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
             }
         }
     }
+    const int lane_wpc = p->word_bytes <= 4 ? 12 : p->word_bytes <= 8 ? 8 : 4;
     const int want_waves =
         p->tun.waves_per_cu > 0 ? p->tun.waves_per_cu * cus
+        : p->lane    ? lane_wpc * cus
         : p->seg_log ? std::min(seg_wpc * cus, std::max(8 * cus, (256 * ndev + nseg - 1) / nseg))
         : wide       ? std::max(4 * cus, std::min(16 * cus, 96 * ndev))
                      : std::max(8 * cus, std::min(24 * cus, 96 * ndev));
     const int target_wpc = p->tun.single_wave ? 1 : std::max(1, (want_waves + cus - 1) / cus);
-    if (!p->seg_log) {
+    if (p->lane) {
+        // LDS: as many of the top frames' classes as fit (all searches of a
+        // wavefront share one limit).  HBM: room for what a search was seen
+        // to use (up to about 100, 250 and 400 classes with the three row
+        // widths); the wavefront's worst-case area takes the rest.
+        const int room = wave_share(std::min(16, target_wpc)) / (2 * 64 * entry);
+        p->lane_kc = std::max(1, std::min(std::max(1, p->mmax), room));
+        const int want = p->word_bytes <= 8 ? 160 : p->word_bytes <= 16 ? 256 : 512;
+        p->cap_classes = std::min(worst_e, std::max(hdr_e + p->mmax, want));
+    } else if (!p->seg_log) {
         // One search per wavefront: the whole worst case, in LDS (at most
         // 2081 classes of 16 bytes for 64 vertices) or, with 128-bit rows,
         // in the wavefront's slice of HBM (up to 264 KB), so a child always
@@ -676,7 +710,7 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
         const int room = max_lds_block / nseg - per_wave(0) / nseg - 16;
         p->cap_classes = std::max(min_cap, std::min(p->cap_classes, room / (2 * p->word_bytes)));
     }
-    p->lds_per_wave = per_wave(p->cap_classes);
+    p->lds_per_wave = p->lane ? 2 * p->lane_kc * 64 * entry : per_wave(p->cap_classes);
     if (p->seg_log)
         p->seg_bytes = p->lds_per_wave / nseg;
     int wpb = 4;
@@ -688,7 +722,7 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
     }
     p->waves_per_block = wpb;
     p->lds_per_block = wpb * p->lds_per_wave;
-    const void *kern = p->seg_log ? mcs_internal_seg_kernel(p->word_bytes, directed, p->seg_log)
+    const void *kern = p->seg_log || p->lane ? mcs_internal_seg_kernel(p->word_bytes, directed, p->seg_log)
                                   : mcs_internal_search_kernel(p->word_bytes, directed,
                                                                p->policy != nullptr);
     int per_cu = 0;
@@ -726,7 +760,12 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
     // (frames placed there start at cap_classes and total at most full_cap
     // classes)
     size_t hstacks = 0;
-    if (wide) {
+    if (p->lane) {
+        p->lane_stride = (int)((mcs::lane_map_bytes_for(p->mmax) + p->cap_classes * entry + 127) / 128 * 128);
+        p->lane_big = worst_e;
+        p->hstack_stride = align256((size_t)64 * p->lane_stride + (size_t)worst_e * entry);
+        hstacks = (size_t)p->waves;
+    } else if (wide) {
         p->hstack_stride = (long long)align256((size_t)(p->cap_classes + 1) * 2 * p->word_bytes);
         hstacks = (size_t)p->waves;
     } else if (p->seg_log && p->cap_classes < full_cap) {
@@ -765,6 +804,11 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
     p->ws_bytes = o;
     *out = p;
     return MCS_OK;
+}
+
+mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H,
+                           const mcs_opts *opts, mcs_plan **out) {
+    return plan_create(count, G, H, opts, out, true);
 }
 
 size_t mcs_plan_workspace_size(const mcs_plan *p) { return p ? p->ws_bytes : 0; }
@@ -824,9 +868,11 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     // (measured on the batched workload: 27-28 s instead of 30-37 s).
     sp.donate_depth = p->tun.donate_depth > 0 ? p->tun.donate_depth : std::max(1, p->mmax);
     // (at most 2^16: the kernel's per-check step counters are 32-bit)
-    sp.check_interval = p->tun.check_interval > 0 ? std::min(p->tun.check_interval, 65536) : 128;
+    sp.check_interval = p->tun.check_interval > 0 ? std::min(p->tun.check_interval, 65536)
+                        : p->lane             ? 16
+                                              : 128;
     sp.reprune = p->tun.no_reprune ? 0 : 1;
-    sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : 32;
+    sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : p->lane ? 4 : 32;
     sp.single_wave = p->tun.single_wave ? 1 : 0;
     sp.policy = p->policy;
     sp.policy_depth = p->policy_depth;
@@ -842,6 +888,10 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.seg_log = p->seg_log;
     sp.seg_bytes = p->seg_bytes;
     sp.arows = p->arows;
+    sp.lane_kc = p->lane_kc;
+    sp.lane_stride = p->lane_stride;
+    sp.lane_map_bytes = mcs::lane_map_bytes_for(p->mmax);
+    sp.lane_big = p->lane_big;
 
     mcs::ResetParams &rp = p->rp;
     rp.inst = sp.inst;
@@ -861,7 +911,7 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
 }
 
 static void *search_fn(const mcs_plan *p) {
-    return p->seg_log ? mcs_internal_seg_kernel(p->word_bytes, p->directed, p->seg_log)
+    return p->seg_log || p->lane ? mcs_internal_seg_kernel(p->word_bytes, p->directed, p->seg_log)
                       : mcs_internal_search_kernel(p->word_bytes, p->directed, p->policy != nullptr);
 }
 
@@ -1433,7 +1483,7 @@ mcs_status mcs_solve_batch_static(int32_t count, const mcs_graph *G, const mcs_g
         return fail(MCS_E_DEVICE, "cannot look up the static scratch's device address (HIP "
                                   "error " + std::to_string(herr) + ")");
     mcs_plan *p = nullptr;
-    mcs_status s = mcs_plan_create(count, G, H, opts, &p);
+    mcs_status s = plan_create(count, G, H, opts, &p, false);
     if (s != MCS_OK)
         return s;
     struct PlanGuard {

@@ -122,7 +122,11 @@ struct SearchParams {
                                      // search per wavefront)
     int seg_bytes;                   // segmented kernel: LDS bytes per search (seg_layout)
     int arows;                       // segmented kernel: adjacency rows kept per graph in LDS
-    int pad_seg;
+    int lane_kc;                     // lane kernel: classes of a top frame kept in LDS
+    int lane_stride;                 // lane kernel: bytes of one lane's stack in HBM
+    int lane_map_bytes;              // ... of which the mapping takes the first
+    int lane_big;                    // lane kernel: entries of a wavefront's worst-case area
+    int pad_lane;
 };
 
 struct ResetParams {
@@ -219,6 +223,16 @@ inline constexpr SegLayout seg_layout(int word_bytes, int directed, int cap_clas
     L.total = align16(L.hdr + frames * 8);
     return L;
 }
+
+// The lane kernel's class stacks in HBM.  An entry is one class; a frame's
+// header takes lane_hdr_entries.  A lane's part: its mapping (8-pair units),
+// then cap entries; a wavefront's 64 parts are followed by one area with room
+// for the worst case, m(m+1)/2 classes and m + 1 headers.
+inline constexpr int lane_hdr_entries(int word_bytes) { return word_bytes == 4 ? 2 : 1; }
+inline constexpr int lane_worst_entries(int word_bytes, int m) {
+    return m * (m + 1) / 2 + (m + 1) * lane_hdr_entries(word_bytes);
+}
+inline constexpr int lane_map_bytes_for(int m) { return align16(2 * (m + 1)); }
 
 inline int slot_bytes_for(int word_bytes, int mmax) {
     int b = rec_header(word_bytes) + 2 * 8 * word_bytes + mmax * 2 * word_bytes;
