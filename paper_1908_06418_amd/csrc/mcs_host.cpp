@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -296,7 +297,7 @@ struct mcs_plan {
     int seg_log = 0;   // 3 or 4: searches of 2^seg_log lanes (mcs_seg.hip); 0: one per wavefront
     int seg_bytes = 0, arows = 0;
     bool lane = false;  // a search in every lane (mcs_lane.hip)
-    int lane_kc = 0, lane_stride = 0, lane_big = 0;
+    int lane_rc = 0, lane_stride = 0, lane_big = 0;
     double tick_hz = 1e8;
 
     uint8_t *ws = nullptr;
@@ -623,7 +624,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     const int hdr_e = mcs::lane_hdr_entries(p->word_bytes), entry = 2 * p->word_bytes;
     const int worst_e = mcs::lane_worst_entries(p->word_bytes, p->mmax);
     const int nseg = p->seg_log ? 64 >> p->seg_log : 1;
-    if (p->seg_log) {
+    if (p->seg_log || p->lane) {
         // adjacency rows a segment keeps: the batch's largest graph, to 4
         int nmax_all = 0;
         for (int i = 0; i < count; i++)
@@ -671,7 +672,26 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
             }
         }
     }
-    const int lane_wpc = p->word_bytes <= 4 ? 12 : p->word_bytes <= 8 ? 8 : 4;
+    // A search in every lane: 4 to 16 wavefronts per CU (8 with wide rows, by
+    // their registers), one per 2^15 nodes that the batch may need.  A tree's
+    // size is taken from its root: unlabelled random pairs double about every
+    // 1.25 vertices (1e4 nodes at 16, 5e5 at 22, 3e7 at 30), labelled ones
+    // every 2.2 matches that Eq. 1 allows at the root.  More wavefronts than
+    // that only cut the work up: one pair G(30, 0.3) takes 6 ms with 4 per CU
+    // and 8 with 16, 60 directed labelled pairs of 40 to 60 vertices 4 and 6,
+    // but 60 pairs G(30, p) 205 and 100.
+    double lane_nodes = 0;
+    for (int i = 0; p->lane && i < ndev; i++)
+        lane_nodes += std::exp2(p->K0[i] <= 1 ? 0.8 * p->m[i] : 0.45 * p->root_bound[i]);
+    int lane_wpc = 4;
+    while (lane_wpc < (wide ? 8 : 16) && lane_nodes > 32768.0 * lane_wpc * cus)
+        lane_wpc += 4;
+    // (a workgroup of up to a CU's wavefronts: they share work through LDS)
+    const int lane_wpb_max = p->word_bytes <= 8 ? 16 : 8;
+    const int lane_rows = p->word_bytes <= 8
+                              ? mcs::align16((directed ? 4 : 2) * p->arows * p->word_bytes)
+                              : 0;
+    const int static_lds = p->lane ? mcs::kLaneTeamBytes : 256;
     const int want_waves =
         p->tun.waves_per_cu > 0 ? p->tun.waves_per_cu * cus
         : p->lane    ? lane_wpc * cus
@@ -680,13 +700,20 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
                      : std::max(8 * cus, std::min(24 * cus, 96 * ndev));
     const int target_wpc = p->tun.single_wave ? 1 : std::max(1, (want_waves + cus - 1) / cus);
     if (p->lane) {
-        // LDS: as many of the top frames' classes as fit (all searches of a
-        // wavefront share one limit).  HBM: room for what a search was seen
-        // to use (up to about 100, 250 and 400 classes with the three row
-        // widths); the wavefront's worst-case area takes the rest.
-        const int room = wave_share(std::min(16, target_wpc)) / (2 * 64 * entry);
-        p->lane_kc = std::max(1, std::min(std::max(1, p->mmax), room));
-        const int want = p->word_bytes <= 8 ? 160 : p->word_bytes <= 16 ? 256 : 512;
+        // LDS: one workgroup holds a CU's wavefronts, its rings what room
+        // there is.  HBM: entries that a search was seen to use (at most
+        // about 130, 160, 250 and 385 with the four row widths); the
+        // wavefront's worst-case area takes the rest.
+        const int wpc = std::min(16, target_wpc);
+        const int per_cu_blocks = (wpc + lane_wpb_max - 1) / lane_wpb_max;
+        const int wpb = (wpc + per_cu_blocks - 1) / per_cu_blocks;
+        const int share = (lds_cu / per_cu_blocks / kLdsGranule * kLdsGranule - static_lds) / wpb;
+        p->lane_rc = std::max(hdr_e + 2, std::min({worst_e, 250, (share - lane_rows) / (64 * entry)}));
+        p->waves_per_block = wpb;
+        const int want = p->word_bytes <= 4    ? 128
+                         : p->word_bytes <= 8  ? 160
+                         : p->word_bytes <= 16 ? 256
+                                               : 384;
         p->cap_classes = std::min(worst_e, std::max(hdr_e + p->mmax, want));
     } else if (!p->seg_log) {
         // One search per wavefront: the whole worst case, in LDS (at most
@@ -704,16 +731,16 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         if (per_wave(full_cap) > wave_share(target_wpc))
             p->cap_classes = std::max(min_cap, seg_cap_at(target_wpc));
     }
-    max_lds_block -= 256;  // the kernel's static LDS (its parameter copy)
+    max_lds_block -= static_lds;
     if (p->seg_log && per_wave(p->cap_classes) > max_lds_block) {
         // one wavefront's stacks must fit in one workgroup's LDS
         const int room = max_lds_block / nseg - per_wave(0) / nseg - 16;
         p->cap_classes = std::max(min_cap, std::min(p->cap_classes, room / (2 * p->word_bytes)));
     }
-    p->lds_per_wave = p->lane ? 2 * p->lane_kc * 64 * entry : per_wave(p->cap_classes);
+    p->lds_per_wave = p->lane ? p->lane_rc * 64 * entry + lane_rows : per_wave(p->cap_classes);
     if (p->seg_log)
         p->seg_bytes = p->lds_per_wave / nseg;
-    int wpb = 4;
+    int wpb = p->lane ? p->waves_per_block : 4;
     while (wpb > 1 && wpb * p->lds_per_wave > max_lds_block)
         wpb >>= 1;
     if (p->lds_per_wave > max_lds_block) {
@@ -740,7 +767,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         // grid's extra workgroups would only start once the first ones end.
         // LDS is counted in whole granules here, on top of the occupancy
         // query.
-        const int blk = (p->lds_per_block + 256 + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
+        const int blk = (p->lds_per_block + static_lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
         per_cu = std::max(1, std::min(per_cu, lds_cu / blk));
     }
     p->blocks = per_cu * cus;
@@ -869,10 +896,10 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.donate_depth = p->tun.donate_depth > 0 ? p->tun.donate_depth : std::max(1, p->mmax);
     // (at most 2^16: the kernel's per-check step counters are 32-bit)
     sp.check_interval = p->tun.check_interval > 0 ? std::min(p->tun.check_interval, 65536)
-                        : p->lane             ? 16
+                        : p->lane             ? 4
                                               : 128;
     sp.reprune = p->tun.no_reprune ? 0 : 1;
-    sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : p->lane ? 4 : 32;
+    sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : p->lane ? 16 : 32;
     sp.single_wave = p->tun.single_wave ? 1 : 0;
     sp.policy = p->policy;
     sp.policy_depth = p->policy_depth;
@@ -888,10 +915,11 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.seg_log = p->seg_log;
     sp.seg_bytes = p->seg_bytes;
     sp.arows = p->arows;
-    sp.lane_kc = p->lane_kc;
+    sp.lane_rc = p->lane_rc;
     sp.lane_stride = p->lane_stride;
     sp.lane_map_bytes = mcs::lane_map_bytes_for(p->mmax);
     sp.lane_big = p->lane_big;
+    sp.check_ticks = p->tun.check_interval > 0 ? 0 : (int)(p->tick_hz * 10e-6);
 
     mcs::ResetParams &rp = p->rp;
     rp.inst = sp.inst;

@@ -18,47 +18,63 @@
 // makes that part's minimum one too large: bound = d + sum instead of
 // d + 1 + sum.
 //
-// Memory of a search:
-//   * its class stack, in HBM (mostly served by L2): frames one after
-//     another, each a header and its classes.  The stack of one lane holds
-//     cap entries; the wavefront has one more area with room for the worst
-//     case, m(m+1)/2 classes and m + 1 headers, which one lane at a time may
-//     continue into when its own part is full (the others wait with the
-//     child that did not fit, or go on with other work);
-//   * in LDS, the first kc classes of its top frame and of that frame's
-//     parent (two buffers, by the parity of the frame's index), so that a
-//     frame is split for all its partners, and a parent is returned to from
-//     a child without children, without touching the HBM copy.  Registers
-//     keep the parent's header for the same case.  A frame is written to the
-//     HBM stack when the search first descends from it.
+// All lanes of a wavefront work on one instance, so its incumbent is a
+// scalar and its adjacency rows (up to 64 vertices) are in LDS once.
+//
+// Memory of a search: a stack of entries of one class each; a frame is a
+// header (lane_hdr_entries) and its classes.  The stack's upper end is in LDS,
+// a ring of rc entries per lane (entry e in slot e mod rc): a frame is
+// created, split for its partners and returned to there, and an entry is
+// written to HBM only when a deeper one needs its slot.  Most of a search's
+// steps stay near the leaves, within the two to four frames that the ring
+// holds.  In HBM a lane's part has room for cap entries; the wavefront has
+// one more area for the worst case, m(m+1)/2 classes and m + 1 headers, which
+// one lane at a time may continue into when its own part is full (the others
+// wait with the child that did not fit, or go on with other work).
 //
 // One step, for the lanes that need each phase:
 //   pop       -- the top frame has nothing left: return to the parent;
 //   unmatched -- its partners are done: bound the "v unmatched" child;
-//   load      -- a frame returned to without its LDS copy is fetched;
+//   fetch     -- a frame returned to that has left the ring comes back;
 //   select    -- a new frame (or one that has just lost v) chooses its class
 //                and v;
-//   evaluate  -- up to kEvals partners w: split and bound, until one
-//                survives;
+//   evaluate  -- the next two partners w: split and bound;
 //   descend   -- the surviving child's non-empty parts become the top frame.
 //
-// Work sharing: idle lanes take whole frames from busy lanes of the same
-// wavefront, all of them at once (steal()): the shallowest open frame below
-// the victim's top, with its remaining partners and its "v unmatched" child.
-// Between wavefronts frames travel as records through the per-XCD rings of
-// mcs_layout.h, one per check.  A record's words are written and read with
-// agent-scope (write-through) accesses, so handing one over needs no
-// write-back or invalidation of an XCD's L2.  A work unit, for the
-// termination counts, is one instance on one wavefront, however many of its
-// lanes work on it.
+// Work sharing, on three levels.  Idle lanes take whole frames from busy
+// lanes of their wavefront, all of them at once (steal()): the lowest open
+// frame of the lanes whose lowest open frame is shallowest.  A wavefront with
+// no work raises its bit in the workgroup's LDS; a busy one that sees it
+// writes a frame straight into the idle one's stack (feed()).  Between
+// workgroups frames travel as records through the per-XCD rings of
+// mcs_layout.h; only one idle wavefront of a workgroup looks there at a time.
+// Each costs one L2-wide release and one acquire, so that the other two levels
+// carry most of the frames.  A work unit, for the termination counts, is one instance on one
+// wavefront, however many of its lanes work on it.
 #include "mcs_device.h"
 
 namespace mcs {
 
 namespace {
 
-constexpr int kEvals = 2;      // partners evaluated per step at most
-constexpr int kPops = 2;       // pop/unmatched rounds per step at most
+// Rounds of pop and unmatched per step: half of the unmatched children are
+// pruned and their lanes pop on (two rounds: the same time within 2%, four
+// too).
+constexpr int kPops = 3;
+// Class reads in flight per lane (narrow rows; 2 with wide ones).
+constexpr int kReads = 4;
+// Idle lanes look for frames in their wavefront once there are so many, or
+// after so many steps (8 to 28 lanes: within 3%).
+constexpr int kIdleLanes = 12, kStealSteps = 8;
+// Frames may lie so much deeper than the shallowest open one to be taken.
+constexpr int kStealSpan = 9;
+// A wavefront feeds waiting siblings once every kFeedSteps while it is rich
+// (so many lanes busy), and now and then anyway.  Feeding at every step cuts
+// the work into units of a few nodes: twice the time on small searches.
+constexpr int kFeedSteps = 4, kFeedRich = 48, kFeedAnyway = 64;
+// A waiting wavefront whose siblings can feed it looks at the rings so much
+// less often.
+constexpr unsigned kFedGap = 16;
 
 // Flags of a search's top frame.
 constexpr int kUnm = 1;        // the "v unmatched" child is still to do
@@ -66,16 +82,16 @@ constexpr int kLe = 2;         // |L_sel| <= |R_sel|: that child's bound is one 
 constexpr int kOne = 4;        // |L_sel| == 1: its class empties with v
 constexpr int kSel = 8;        // class and v are to be chosen
 constexpr int kPatch = 16;     // (with kSel) v is to be taken out of the selected class first
-constexpr int kDirty = 32;     // the HBM copy is missing or old
-constexpr int kInLds = 64;     // the LDS buffer holds the frame's first kc classes
-constexpr int kRow = 128;      // v's G rows are to be loaded
+constexpr int kRow = 32;       // v's G rows are to be loaded
 constexpr int kBig = 8;        // (saved headers) the child frame starts the worst-case area
 constexpr int kSaved = kUnm | kLe | kOne;
 
 constexpr unsigned kErrMapping = 2;  // codes of DevGlobals::error
 constexpr unsigned kErrStack = 3;
+constexpr unsigned kErrRecord = 1;
 
-typedef unsigned long long v2u64 __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64w;
+typedef u64w v2u64 __attribute__((ext_vector_type(2)));
 typedef v2u64 v2u64_a8 __attribute__((aligned(8)));
 template <typename T>
 using lds_ptr = __attribute__((address_space(3))) T *;
@@ -83,14 +99,34 @@ using lds_ptr = __attribute__((address_space(3))) T *;
 template <typename T>
 using glb_ptr = __attribute__((address_space(1))) T *;
 
+// The launch parameters where the kernel got them: scalar loads, so that a
+// field that is needed now and then takes no register in between.
+using KernArgs = __attribute__((address_space(4))) SearchParams;
+
 // Lane `from`'s x (every lane of the wavefront active).
 DEV int shfl_any(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
 
-// 64-bit words of a queued record, written and read past the L2s' private
-// lines (agent scope), so that no fence has to write back or invalidate one.
-DEV void st_agent(unsigned long long *p, unsigned long long v) { st_rlx(p, v); }
-DEV unsigned long long ld_agent(const unsigned long long *p) {
-    return ld_rlx((unsigned long long *)p);
+// What the wavefronts of a workgroup share.
+struct Team {
+    unsigned hungry;      // bit w: wavefront w waits for a frame
+    unsigned done;        // the search is over
+    unsigned looked;      // ticks of the last look at the rings (low word)
+    unsigned idle;        // 1: the workgroup is counted as idle
+    unsigned full[16];    // 1: a frame for wavefront w is in its stack, its
+    u64w box[16][6];      //    header here (x, y; unit; partners)
+    // work units: one instance each, on one or more of the wavefronts
+    unsigned ref[16];     // 0: free; 1 + the wavefronts on it
+    int inst[16];
+    int inc[16];          // the incumbent as last seen or raised
+    unsigned seen[16];    // ticks of the last look at it
+    u64w nodes[16];       // counted by wavefronts that have left
+};
+static_assert(sizeof(Team) <= kLaneTeamBytes, "the host leaves room for it in LDS");
+template <typename T>
+DEV T ld_wg(T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+template <typename T>
+DEV void st_wg(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 }  // namespace
@@ -100,9 +136,14 @@ struct LaneSearch {
     static constexpr int NB = bits_of<W>();
     static constexpr int NR = DIR ? 4 : 2;                  // row sets, and parts of a class
     static constexpr int EB = 2 * (int)sizeof(W);           // bytes of a stack entry: one class
+    static constexpr int EW = EB / 8;                       // its 64-bit words
     static constexpr int HE = lane_hdr_entries((int)sizeof(W));  // entries of a frame header
-    static constexpr int NP = EB >= 16 ? EB / 16 : 1;       // 16-byte pieces of a class
+    static constexpr int NP = EB >= 16 ? EB / 16 : 1;       // 16-byte pieces of an entry
+    static constexpr bool LROWS = sizeof(W) <= 8;           // rows in LDS
 
+    struct Ent {
+        u64w w[EW];
+    };
     // A frame header: two 32-bit words and the partners left.
     //   x: base of the frame below (16 bits) | K << 16 | d << 24
     //   y: v | sel << 8 | bound << 16 | flags << 24
@@ -111,210 +152,253 @@ struct LaneSearch {
         W r;
     };
 
-    const SearchParams &P;
-    int cap, kc, reprune;
-    int lane;
+    const KernArgs &P;
+    Team &T;
+    int cap, rc, reprune, arows;
+    float rinv;          // 1 / rc
+    int lane, wv;
     uint32_t stride, map_bytes, big_off, big_cap;
     glb_ptr<char> wst;   // the wavefront's stacks in HBM
-    lds_ptr<char> lbuf;  // the wavefront's class buffers: [2][kc][64 lanes], NP planes
-    const W *gadj;
+    lds_ptr<char> lbuf;  // the wavefront's rings: [rc][64 lanes], NP planes
+    lds_ptr<W> lrow;     // (up to 64 vertices) the instance's rows: [NR][arows]
+    const W *grow;       // the instance's rows in HBM: [NR][NB]
 
     // ---- per-lane state ----
-    int inst, inc, target;
-    int t, base, pbase, K, d, v, sel, bound, flags;
+    int t, base, pbase, bslot, K, d, v, sel, bound, flags;
     int lo_t, lo_base;   // the lowest frame that may still have work
+    int wlo, wslot;      // the ring's lowest entry, and its slot
     W rrem, go, gi;
-    const W *rows;       // the instance's adjacency rows: [NR][NB]
-    bool pv;             // c_*: the parent's header; its LDS buffer is intact
-    uint32_t c_x, c_y;
-    W c_r;
-    bool fin;
     uint32_t c_child, c_unm, c_ncls, c_pushed;  // since the last flush
     int max_used;
 
     // ---- wave-level ----
+    int inst, rows_inst, inc, target, inc_slot, twin, dead_on;
+    int unit;            // the unit the wavefront works on, or -1
     bool stop, roots_left;
-    int my_ring, steal_from, since_check;
-    unsigned long long t_start, n_steps, n_don, n_pops, n_busy, n_sleep, n_big;
-    unsigned long long n_child, n_ncls, n_pushed;  // (per lane)
+    int my_ring, steal_from, other, since_check;
+    u64w t_start, n_steps, n_don, n_pops, n_busy, n_sleep, n_big;
+    u64w n_child, n_ncls, n_pushed;
 
-    __device__ LaneSearch(const SearchParams &p, lds_ptr<char> lds, long long wave) : P(p) {
+    __device__ LaneSearch(const KernArgs &p, Team &tm, lds_ptr<char> lds, int wave_in_block,
+                          long long wave)
+        : P(p), T(tm) {
         lane = lane_id();
+        wv = wave_in_block;
         cap = sc(p.cap_classes);
-        kc = sc(p.lane_kc);
+        rc = sc(p.lane_rc);
+        rinv = 1.0f / (float)rc;
         reprune = sc(p.reprune);
+        arows = sc(p.arows);
         stride = (uint32_t)sc(p.lane_stride);
         map_bytes = (uint32_t)sc(p.lane_map_bytes);
         big_off = 64u * stride;
         big_cap = (uint32_t)sc(p.lane_big);
         wst = (glb_ptr<char>)(p.hstack + (size_t)wave * (size_t)p.hstack_stride);
         lbuf = lds;
-        gadj = (const W *)p.adj;
-        inst = -1;
-        inc = target = 0;
+        lrow = (lds_ptr<W>)(lds + rc * 64 * EB);
+        grow = (const W *)p.adj;
+        inst = rows_inst = -1;
+        inc = target = inc_slot = dead_on = 0;
+        twin = -1;
+        unit = -1;
         t = -1;
-        base = pbase = K = d = v = sel = bound = flags = 0;
-        lo_t = lo_base = 0;
+        base = pbase = bslot = K = d = v = sel = bound = flags = 0;
+        lo_t = lo_base = wlo = wslot = 0;
         rrem = go = gi = (W)0;
-        rows = gadj;
-        pv = false;
-        c_x = c_y = 0;
-        c_r = (W)0;
-        fin = false;
         c_child = c_unm = c_ncls = c_pushed = 0;
         max_used = 0;
         stop = false;
         roots_left = true;
         my_ring = (int)(blockIdx.x & (kRings - 1));
-        steal_from = my_ring;
+        steal_from = other = my_ring;
         since_check = 0;
         t_start = n_steps = n_don = n_pops = n_busy = n_sleep = n_big = 0;
         n_child = n_ncls = n_pushed = 0;
     }
 
-    // ---- the stack in HBM ----
+    // ---- stack entries ----
 
-    // Byte offset of entry i of lane l's stack: its own part below cap, the
-    // wavefront's worst-case area from cap on.
-    __device__ uint32_t at(int l, int i) const {
-        return i < cap ? (uint32_t)l * stride + map_bytes + (uint32_t)i * EB
-                       : big_off + (uint32_t)(i - cap) * EB;
+    // Byte offset of entry e of lane l's stack in HBM: its own part below
+    // cap, the wavefront's worst-case area from cap on.
+    __device__ uint32_t at(int l, int e) const {
+        return e < cap ? (uint32_t)l * stride + map_bytes + (uint32_t)e * EB
+                       : big_off + (uint32_t)(e - cap) * EB;
     }
-    // (entries of 32-bit rows are 8 bytes: no more alignment than that)
-    __device__ v2u64 ld16(uint32_t off) const { return *(glb_ptr<v2u64_a8>)(wst + off); }
-    __device__ void st16(uint32_t off, unsigned long long a, unsigned long long b) const {
-        v2u64 x = {a, b};
-        *(glb_ptr<v2u64_a8>)(wst + off) = x;
+    // Slot of entry e (e < 2^16 and rc < 2^8: the rounded quotient is exact).
+    __device__ int slot_of(int e) const {
+        return e - rc * (int)(((float)e + 0.5f) * rinv);
     }
-    __device__ Cls<W> gget(uint32_t off) const {
+    __device__ int wrap(int s) const {  // s < 2 rc
+        return (int)umin((uint32_t)s, (uint32_t)(s - rc));
+    }
+    __device__ Ent hget(uint32_t off) const {
+        Ent x;
+        if constexpr (EW == 1) {
+            x.w[0] = *(glb_ptr<u64w>)(wst + off);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const v2u64 q = *(glb_ptr<v2u64_a8>)(wst + off + 16 * i);
+                x.w[2 * i] = q[0];
+                x.w[2 * i + 1] = q[1];
+            }
+        }
+        return x;
+    }
+    __device__ void hput(uint32_t off, const Ent &x) const {
+        if constexpr (EW == 1) {
+            *(glb_ptr<u64w>)(wst + off) = x.w[0];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                v2u64 q = {x.w[2 * i], x.w[2 * i + 1]};
+                *(glb_ptr<v2u64_a8>)(wst + off + 16 * i) = q;
+            }
+        }
+    }
+    __device__ Ent lget(int l, int slot) const {
+        const int i = slot * 64 + l;
+        Ent x;
+        if constexpr (EW == 1) {
+            x.w[0] = ((lds_ptr<u64w>)lbuf)[i];
+        } else {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const v2u64 q = ((lds_ptr<v2u64>)lbuf)[i + j * 64 * rc];
+                x.w[2 * j] = q[0];
+                x.w[2 * j + 1] = q[1];
+            }
+        }
+        return x;
+    }
+    __device__ void lput(int l, int slot, const Ent &x) const {
+        const int i = slot * 64 + l;
+        if constexpr (EW == 1) {
+            ((lds_ptr<u64w>)lbuf)[i] = x.w[0];
+        } else {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                v2u64 q = {x.w[2 * j], x.w[2 * j + 1]};
+                ((lds_ptr<v2u64>)lbuf)[i + j * 64 * rc] = q;
+            }
+        }
+    }
+    // Entry e of lane l's stack, whose ring starts at wl.
+    __device__ Ent eget(int l, int e, int wl) const {
+        return e >= wl ? lget(l, slot_of(e)) : hget(at(l, e));
+    }
+    __device__ void eput(int l, int e, int wl, const Ent &x) const {
+        if (e >= wl)
+            lput(l, slot_of(e), x);
+        else
+            hput(at(l, e), x);
+    }
+    DEV Ent pack(const Cls<W> &c) {
+        Ent x;
+        if constexpr (EW == 1) {
+            x.w[0] = (u64w)(uint32_t)c.L | ((u64w)(uint32_t)c.R << 32);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                x.w[i] = word64(c.L, i);
+                x.w[NP + i] = word64(c.R, i);
+            }
+        }
+        return x;
+    }
+    DEV Cls<W> unpack(const Ent &x) {
         Cls<W> c;
-        if constexpr (sizeof(W) == 4) {
-            const unsigned long long x = *(glb_ptr<unsigned long long>)(wst + off);
-            c.L = (uint32_t)x;
-            c.R = (uint32_t)(x >> 32);
+        if constexpr (EW == 1) {
+            c.L = (W)(uint32_t)x.w[0];
+            c.R = (W)(uint32_t)(x.w[0] >> 32);
         } else {
             uint64_t w[2 * NP];
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const v2u64 x = ld16(off + 16 * i);
-                w[2 * i] = x[0];
-                w[2 * i + 1] = x[1];
-            }
+            for (int i = 0; i < 2 * NP; ++i)
+                w[i] = x.w[i];
             c.L = from_words<W>(w);
             c.R = from_words<W>(w + NP);
         }
         return c;
     }
-    __device__ void gput(uint32_t off, const Cls<W> &c) const {
-        if constexpr (sizeof(W) == 4) {
-            *(glb_ptr<unsigned long long>)(wst + off) =
-                (unsigned long long)(uint32_t)c.L | ((unsigned long long)(uint32_t)c.R << 32);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int j = 2 * i;
-                st16(off + 16 * i, j < NP ? word64(c.L, j) : word64(c.R, j - NP),
-                     j + 1 < NP ? word64(c.L, j + 1) : word64(c.R, j + 1 - NP));
-            }
-        }
-    }
-    __device__ Hdr ld_hdr(uint32_t off) const {
+    __device__ Hdr get_hdr(int l, int e, int wl) const {
         Hdr h;
-        const v2u64 a = ld16(off);
-        h.x = (uint32_t)a[0];
-        h.y = (uint32_t)(a[0] >> 32);
-        if constexpr (sizeof(W) <= 8) {
-            h.r = (W)a[1];
+        const Ent a = eget(l, e, wl);
+        h.x = (uint32_t)a.w[0];
+        h.y = (uint32_t)(a.w[0] >> 32);
+        if constexpr (EW == 1) {
+            h.r = (W)(uint32_t)eget(l, e + 1, wl).w[0];
         } else {
             uint64_t w[NP];
 #pragma unroll
-            for (int i = 0; i < NP / 2; ++i) {
-                const v2u64 x = ld16(off + 16 + 16 * i);
-                w[2 * i] = x[0];
-                w[2 * i + 1] = x[1];
-            }
+            for (int i = 0; i < NP; ++i)
+                w[i] = a.w[1 + i];
             h.r = from_words<W>(w);
         }
         return h;
     }
-    __device__ void st_hdr(uint32_t off, const Hdr &h) const {
-        const unsigned long long a = (unsigned long long)h.x | ((unsigned long long)h.y << 32);
-        if constexpr (sizeof(W) <= 8) {
-            st16(off, a, (unsigned long long)h.r);
+    __device__ void put_hdr(int l, int e, int wl, const Hdr &h) const {
+        Ent a = {};
+        a.w[0] = (u64w)h.x | ((u64w)h.y << 32);
+        if constexpr (EW == 1) {
+            eput(l, e, wl, a);
+            Ent b;
+            b.w[0] = (u64w)(uint32_t)h.r;
+            eput(l, e + 1, wl, b);
         } else {
-            st16(off, a, 0);
 #pragma unroll
-            for (int i = 0; i < NP / 2; ++i)
-                st16(off + 16 + 16 * i, word64(h.r, 2 * i), word64(h.r, 2 * i + 1));
+            for (int i = 0; i < NP; ++i)
+                a.w[1 + i] = word64(h.r, i);
+            eput(l, e, wl, a);
         }
     }
     __device__ glb_ptr<uint16_t> map_at(int l) const {
         return (glb_ptr<uint16_t>)(wst + (uint32_t)l * stride);
     }
+    // Class k of the lane's top frame.
+    __device__ Cls<W> cget(int k) const { return unpack(eget(lane, base + HE + k, wlo)); }
+    __device__ void cput(int k, const Cls<W> &c) const { eput(lane, base + HE + k, wlo, pack(c)); }
 
-    // ---- the top frame's classes ----
-
-    // Class k (< kc) of lane l's LDS buffer `par`.
-    __device__ Cls<W> lget(int l, int par, int k) const {
-        const int i = (par * kc + k) * 64 + l;
-        Cls<W> c;
-        if constexpr (sizeof(W) == 4) {
-            const unsigned long long x = ((lds_ptr<unsigned long long>)lbuf)[i];
-            c.L = (uint32_t)x;
-            c.R = (uint32_t)(x >> 32);
-        } else {
-            uint64_t w[2 * NP];
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const v2u64 x = ((lds_ptr<v2u64>)lbuf)[i + j * 128 * kc];
-                w[2 * j] = x[0];
-                w[2 * j + 1] = x[1];
-            }
-            c.L = from_words<W>(w);
-            c.R = from_words<W>(w + NP);
-        }
-        return c;
-    }
-    __device__ void lput(int l, int par, int k, const Cls<W> &c) const {
-        const int i = (par * kc + k) * 64 + l;
-        if constexpr (sizeof(W) == 4) {
-            ((lds_ptr<unsigned long long>)lbuf)[i] =
-                (unsigned long long)(uint32_t)c.L | ((unsigned long long)(uint32_t)c.R << 32);
-        } else {
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const int q = 2 * j;
-                v2u64 x = {q < NP ? word64(c.L, q) : word64(c.R, q - NP),
-                           q + 1 < NP ? word64(c.L, q + 1) : word64(c.R, q + 1 - NP)};
-                ((lds_ptr<v2u64>)lbuf)[i + j * 128 * kc] = x;
-            }
-        }
-    }
-    // Class k of the lane's own top frame (in its LDS buffer, or past it).
-    __device__ Cls<W> cget(int k) const {
-        return k < kc ? lget(lane, t & 1, k) : gget(at(lane, base + HE + k));
-    }
-    __device__ void cput(int k, const Cls<W> &c) const {
-        if (k < kc)
-            lput(lane, t & 1, k, c);
-        else
-            gput(at(lane, base + HE + k), c);
-    }
-    // f(k, class k, k < kc) for each class of the top frames of the lanes
-    // that call this, in step.
+    // f(class k) for each class of the top frames of the lanes that call
+    // this, in step.  far: some lane's frame is not all in its ring, or may
+    // lose entries to the calls.
     template <typename F>
-    __device__ void each_class(F f) const {
-        const int par = t & 1;
-        int k = 0;
-        for (; k < kc && ballot(k < K) != 0; ++k)
-            if (k < K)
-                f(k, lget(lane, par, k), true);
-        if (ballot(k < K) != 0) {
-            const uint32_t off = at(lane, base + HE);
-            for (; ballot(k < K) != 0; ++k)
+    __device__ void each_class(bool far, F f) const {
+        if (!far) {
+            // (U reads in flight at a time)
+            constexpr int U = EW <= 2 ? kReads : 2;
+            int s = wrap(bslot + HE);
+            for (int k = 0; ballot(k < K) != 0; k += U) {
+                Ent x[U];
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    x[i] = lget(lane, s);
+                    s = wrap(s + 1);
+                }
+#pragma unroll
+                for (int i = 0; i < U; ++i)
+                    if (k + i < K)
+                        f(k + i, unpack(x[i]));
+            }
+        } else {
+            for (int k = 0; ballot(k < K) != 0; ++k)
                 if (k < K)
-                    f(k, gget(off + (uint32_t)k * EB), false);
+                    f(k, cget(k));
         }
+    }
+
+    // The ring's lowest entry goes to HBM.
+    __device__ void evict() {
+        hput(at(lane, wlo), lget(lane, wslot));
+        wlo += 1;
+        wslot = wrap(wslot + 1);
+    }
+
+    __device__ W row(int set, int i) const {
+        if constexpr (LROWS)
+            return lrow[set * arows + i];
+        else
+            return ld_w(grow + set * NB + i);
     }
 
     // ---- incumbent ----
@@ -324,27 +408,48 @@ struct LaneSearch {
         x = cap_inc(x);
         inc = x > inc ? x : inc;
     }
+    // The incumbent, or 255 where the instance needs no more search.
+    __device__ int read_inc() const {
+        int g = 0;
+        if (lane == 0) {
+            g = ld_rlx(&P.inc[inc_slot]);
+            if (twin >= 0 && ld_rlx(&P.open[twin]) == 0 && !ld_rlx(&P.dead[twin]))
+                g = 255;  // the twin's search already finished
+            if (dead_on && ld_rlx(&P.dead[inst]))
+                g = 255;  // given up as a dead end
+        }
+        return rl(g, 0);
+    }
 
-    // The path of this lane's map (size vertex pairs) is a common induced
-    // subgraph: raise the instance's incumbent; the search that raised it to
-    // `size` writes that size's mapping slot.
-    __device__ void improve(int size) {
+    // Lane l's map (size vertex pairs) is a common induced subgraph: raise
+    // the instance's incumbent; the wavefront that raised it to `size` writes
+    // that size's mapping slot.
+    __device__ void improve(int l, int size) {
         const DevInst di = P.inst[inst];
-        if (size > (di.nG < di.nH ? (int)di.nG : (int)di.nH)) {
-            fail_lane(kErrMapping);  // only from a broken class partition
+        if (size > sc(di.nG < di.nH ? (int)di.nG : (int)di.nH)) {
+            fail(kErrMapping);  // only from a broken class partition
             return;
         }
-        const int old = a_max(&P.inc[di.inc_slot], size);
+        int old = 0;
+        if (lane == 0)
+            old = a_max(&P.inc[inc_slot], size);
+        old = rl(old, 0);
         if (old < size) {
+            wave_sync();
             uint16_t *dst = P.maps + di.map_off + size * (size - 1) / 2;
-            const glb_ptr<uint16_t> m = map_at(lane);
-            for (int j = 0; j < size; ++j)
+            const glb_ptr<uint16_t> m = map_at(l);
+            for (int j = lane; j < size; j += 64)
                 dst[j] = m[j];
-            a_max64(&P.t_best[inst], ((unsigned long long)size << 48) |
-                                         (now_ticks() & 0xFFFFFFFFFFFFull));
-            a_max64(&P.best_nodes[inst], ld_rlx(&P.nodes[inst]) + c_child + c_unm);
+            const u64w pend = lanes_total(c_child) + lanes_total(c_unm);
+            if (lane == 0) {
+                a_max64(&P.t_best[inst], ((u64w)size << 48) | (now_ticks() & 0xFFFFFFFFFFFFull));
+                a_max64(&P.best_nodes[inst], ld_rlx(&P.nodes[inst]) + pend);
+            }
         }
         set_inc(old > size ? old : size);
+        if (lane == 0)
+            __hip_atomic_fetch_max(&T.inc[unit], inc, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 
     // ---- the phases of a step ----
@@ -352,23 +457,12 @@ struct LaneSearch {
     __device__ void pop() {
         rrem = (W)0;
         flags = 0;
-        if (t == 0) {
-            t = -1;
-            fin = true;
-            return;
-        }
         t -= 1;
-        Hdr h;
-        if (pv) {
-            h.x = c_x;
-            h.y = c_y;
-            h.r = c_r;
-            flags = kInLds;
-        } else {
-            h = ld_hdr(at(lane, pbase));
-        }
-        pv = false;
+        if (t < 0)
+            return;
         base = pbase;
+        bslot = slot_of(base);
+        const Hdr h = get_hdr(lane, base, wlo);
         pbase = (int)(h.x & 0xFFFFu);
         K = (int)((h.x >> 16) & 0xFFu);
         d = (int)(h.x >> 24);
@@ -379,11 +473,9 @@ struct LaneSearch {
             lo_t = t;
             lo_base = base;
         }
-        if (reprune && bound <= inc) {
-            flags = 0;  // nothing here can beat the incumbent: pop again
-            return;
-        }
-        flags |= (int)(h.y >> 24) & kSaved;
+        if (reprune && bound <= inc)
+            return;  // nothing here can beat the incumbent: pop again
+        flags = (int)(h.y >> 24) & kSaved;
         rrem = h.r;
         if (rrem != (W)0)
             flags |= kRow;
@@ -399,17 +491,30 @@ struct LaneSearch {
             return;
         }
         bound = ub;
-        flags = (flags & (kOne | kInLds | kDirty)) | kSel | kPatch;
+        flags = (flags & kOne) | kSel | kPatch;
     }
 
-    // The first kc classes of a frame returned to, back into its buffer.
+    // The top frame (its upper rc entries) back into the ring.
     __device__ void fetch() {
-        const uint32_t off = at(lane, base + HE);
-        const int n = K < kc ? K : kc;
-        for (int k = 0; ballot(k < n) != 0; ++k)
-            if (k < n)
-                lput(lane, t & 1, k, gget(off + (uint32_t)k * EB));
-        flags |= kInLds;
+        const int end = base + HE + K;
+        const int lo = end - rc > base ? end - rc : base;
+        const int hi = wlo < end ? wlo : end;
+        int s = slot_of(lo);
+        wlo = lo;
+        wslot = s;
+        for (int e = lo; ballot(e < hi) != 0; e += 4) {
+            // (four loads in flight; past hi the last entry again)
+            Ent x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                x[i] = hget(at(lane, e + i < hi ? e + i : hi - 1));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (e + i < hi)
+                    lput(lane, s, x[i]);
+                s = wrap(s + 1);
+            }
+        }
     }
 
     __device__ void select() {
@@ -424,11 +529,10 @@ struct LaneSearch {
                 c.L = c.L & ~bit_at<W>(v);
                 cput(sel, c);
             }
-            flags |= kDirty;
         }
         // the class of smallest max(|L|, |R|), ties to the smallest G vertex
         uint32_t key = 0xFFFFFFFFu;
-        each_class([&](int k, const Cls<W> &c, bool) {
+        each_class(ballot(base < wlo) != 0, [&](int k, const Cls<W> &c) {
             const int nl = popc(c.L), nr = popc(c.R);
             key = umin(key, ((uint32_t)(nl > nr ? nl : nr) << 16) | ((uint32_t)ctz(c.L) << 8) |
                                 (uint32_t)k);
@@ -438,8 +542,7 @@ struct LaneSearch {
         const Cls<W> c = cget(sel);
         const int nl = popc(c.L), nr = popc(c.R);
         rrem = c.R;
-        flags = (flags & (kDirty | kInLds)) | kUnm | kRow | (nl <= nr ? kLe : 0) |
-                (nl == 1 ? kOne : 0);
+        flags = kUnm | kRow | (nl <= nr ? kLe : 0) | (nl == 1 ? kOne : 0);
     }
 
     // Parts of class c for the child (v, w) by adjacency letter; v and w are
@@ -464,53 +567,83 @@ struct LaneSearch {
         }
     }
 
-    // The next partner w of v: the child's Eq. 1 bound.
+    // The next two partners of v (or the one that is left): their children's
+    // Eq. 1 bounds, from one pass over the classes and one count of v's side.
+    // The first that survives is (w, b); a second one that is pruned is done
+    // too, one that would survive waits until the search is back.
     __device__ bool evaluate(int &w, int &b) {
-        w = ctz(rrem);
-        rrem = rrem & (rrem - (W)1);
-        const W ho = ld_w(rows + NB + w);
-        W hi = (W)0;
-        if constexpr (DIR)
-            hi = ld_w(rows + 3 * NB + w);
-        int sum = d;  // (v and w each count once in the selected class: d + 1 - 1)
-        each_class([&](int, const Cls<W> &c, bool) {
+        const int w0 = ctz(rrem);
+        const W r1 = rrem & (rrem - (W)1);
+        const bool two = r1 != (W)0;
+        const int w1 = two ? ctz(r1) : w0;
+        const W ho0 = row(1, w0), ho1 = row(1, w1);
+        W hi0 = (W)0, hi1 = (W)0;
+        if constexpr (DIR) {
+            hi0 = row(3, w0);
+            hi1 = row(3, w1);
+        }
+        int s0 = d, s1 = d;  // (v and w each count once in the selected class: d + 1 - 1)
+        each_class(ballot(base < wlo) != 0, [&](int, const Cls<W> &c) {
             if constexpr (!DIR) {
-                const int l1 = popc(c.L & go), r1 = popc(c.R & ho);
-                const int l0 = popc(c.L) - l1, r0 = popc(c.R) - r1;
-                sum += (l1 < r1 ? l1 : r1) + (l0 < r0 ? l0 : r0);
+                const int l1 = popc(c.L & go), l0 = popc(c.L) - l1, rt = popc(c.R);
+                const int x = popc(c.R & ho0), y = popc(c.R & ho1);
+                s0 += (l1 < x ? l1 : x) + (l0 < rt - x ? l0 : rt - x);
+                s1 += (l1 < y ? l1 : y) + (l0 < rt - y ? l0 : rt - y);
             } else {
-                W pl[4], pr[4];
-                split(c, ho, hi, pl, pr);
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const int nl = popc(pl[a]), nr = popc(pr[a]);
-                    sum += nl < nr ? nl : nr;
-                }
+                const W lo1 = c.L & go;
+                const int l3 = popc(lo1 & gi), l1 = popc(lo1) - l3, l2 = popc(c.L & gi) - l3;
+                const int l0 = popc(c.L) - l1 - l2 - l3, rt = popc(c.R);
+                const auto add = [&](const W &ho, const W &hi, int &s) {
+                    const W ro1 = c.R & ho;
+                    const int r3 = popc(ro1 & hi), q1 = popc(ro1) - r3, q2 = popc(c.R & hi) - r3;
+                    const int q0 = rt - q1 - q2 - r3;
+                    s += (l0 < q0 ? l0 : q0) + (l1 < q1 ? l1 : q1) + (l2 < q2 ? l2 : q2) +
+                         (l3 < r3 ? l3 : r3);
+                };
+                add(ho0, hi0, s0);
+                add(ho1, hi1, s1);
             }
         });
-        b = sum;
-        c_child += 1;
-        c_ncls += (uint32_t)K;
-        return sum > inc;
+        const bool f0 = s0 > inc, f1 = two && s1 > inc;
+        const bool second = two && !(f0 && f1);  // it is done as well
+        rrem = second ? r1 & (r1 - (W)1) : r1;
+        c_child += second ? 2u : 1u;
+        c_ncls += (uint32_t)(second ? 2 * K : K);
+        w = f0 ? w0 : w1;
+        b = f0 ? s0 : s1;
+        return f0 || f1;
     }
 
-    // The child (v, w) of bound b becomes the top frame: its non-empty
-    // classes, each side non-empty.  Each of them adds at least one to b, so
-    // there are at most b - d - 1.  nb: where its frame starts.
+    // The child (v, w) of bound b becomes the top frame: its classes with
+    // both sides non-empty.  Each of them adds at least one to b, so there
+    // are at most b - d - 1.  nb: where its frame starts.
     __device__ void descend(int w, int b, int nb) {
-        const W ho = ld_w(rows + NB + w);
+        const W ho = row(1, w);
         W hi = (W)0;
         if constexpr (DIR)
-            hi = ld_w(rows + 3 * NB + w);
-        const uint32_t own = at(lane, base + HE);
-        const uint32_t sub = at(lane, nb + HE);
-        const int npar = (t + 1) & 1;
-        const bool save = (flags & kDirty) != 0;
+            hi = row(3, w);
         const W vb = bit_at<W>(v), wb = bit_at<W>(w);
-        int K2 = 0;
-        each_class([&](int k, const Cls<W> &c, bool lds) {
-            if (lds && save)
-                gput(own + (uint32_t)k * EB, c);
+        if (ballot(nb >= cap && base < cap) != 0) {
+            // entries jump to the worst-case area: the ring starts anew there
+            if (nb >= cap && base < cap) {
+                for (int n = base + HE + K - wlo; n > 0; --n)
+                    evict();
+                wlo = nb;
+                wslot = slot_of(nb);
+            }
+        }
+        // Class k is still in the ring when its turn comes: the k classes
+        // before it left at most NR k parts, which pushed out at most
+        // (K + 2 HE + NR k) - rc entries of this frame, at most HE + k.
+        const bool far = ballot(base < wlo || K + HE + (NR - 1) * (K - 1) > rc) != 0;
+        // the child's header, written when the search leaves it for a child
+        for (int i = 0; i < HE; ++i)
+            if (nb + i - wlo >= rc)
+                evict();
+        const int cslot = slot_of(nb);
+        int s = wrap(cslot + HE), K2 = 0;
+        int room = rc - (nb + HE - wlo);  // parts that fit before entries must go
+        each_class(far, [&](int, const Cls<W> &c) {
             W pl[NR], pr[NR];
             split(c, ho, hi, pl, pr);
             pl[0] = pl[0] & ~vb;
@@ -518,53 +651,48 @@ struct LaneSearch {
 #pragma unroll
             for (int a = 0; a < NR; ++a) {
                 if (pl[a] != (W)0 && pr[a] != (W)0) {
+                    if (K2 >= room) {
+                        evict();
+                        room += 1;
+                    }
                     Cls<W> x;
                     x.L = pl[a];
                     x.R = pr[a];
-                    if (K2 < kc)
-                        lput(lane, npar, K2, x);
-                    else
-                        gput(sub + (uint32_t)K2 * EB, x);
+                    lput(lane, s, pack(x));
+                    s = wrap(s + 1);
                     K2 += 1;
                 }
             }
         });
-        flags &= ~kDirty;
+        map_at(lane)[d] = (uint16_t)(v | (w << 8));
+        if (K2 == 0)
+            return;  // nothing left to split: the parent goes on
         Hdr h;
         h.x = (uint32_t)pbase | ((uint32_t)K << 16) | ((uint32_t)d << 24);
         h.y = (uint32_t)v | ((uint32_t)sel << 8) | ((uint32_t)bound << 16) |
               ((uint32_t)(flags & kSaved) << 24) |
               ((base < cap && nb >= cap) ? (uint32_t)kBig << 24 : 0u);
         h.r = rrem;
-        map_at(lane)[d] = (uint16_t)(v | (w << 8));
-        if (d + 1 > inc)
-            improve(d + 1);
-        if (K2 == 0)
-            return;  // nothing left to split: the parent goes on
-        st_hdr(at(lane, base), h);
-        c_x = h.x;
-        c_y = h.y;
-        c_r = h.r;
-        pv = true;
+        put_hdr(lane, base, wlo, h);
         c_pushed += (uint32_t)K2;
         pbase = base;
         base = nb;
+        bslot = cslot;
         t += 1;
         K = K2;
         d += 1;
         bound = b;
         rrem = (W)0;
-        flags = kSel | kDirty | kInLds;
+        flags = kSel;
         const int used = nb + HE + K2;
         max_used = used > max_used ? used : max_used;
     }
 
     __device__ void step() {
-        // pop and unmatched, twice if lanes need it: half of the unmatched
-        // children are pruned, and their lanes pop on
+        // pop and unmatched, in turns while lanes need them: half of the
+        // unmatched children are pruned, and their lanes pop on
         for (int i = 0; i < kPops; ++i) {
-            const bool need_pop =
-                t >= 0 && rrem == (W)0 && !(flags & (kUnm | kSel));
+            const bool need_pop = t >= 0 && rrem == (W)0 && !(flags & (kUnm | kSel));
             if (ballot(need_pop)) {
                 if (need_pop)
                     pop();
@@ -576,7 +704,8 @@ struct LaneSearch {
                 if (need_unm)
                     unmatched();
         }
-        const bool need_ld = (rrem != (W)0 || (flags & kSel)) && !(flags & kInLds);
+        const bool need_ld = (rrem != (W)0 || (flags & kSel)) && base < wlo &&
+                             (wlo > base + HE + K - rc);
         if (ballot(need_ld))
             if (need_ld)
                 fetch();
@@ -585,20 +714,16 @@ struct LaneSearch {
             if (need_sel)
                 select();
         if (flags & kRow) {
-            go = ld_w(rows + v);
+            go = row(0, v);
             if constexpr (DIR)
-                gi = ld_w(rows + 2 * NB + v);
+                gi = row(2, v);
             flags &= ~kRow;
         }
         bool found = false;
         int w = 0, b = 0;
-        for (int i = 0; i < kEvals; ++i) {
-            const bool ev = rrem != (W)0 && !found;
-            if (ballot(ev) == 0)
-                break;
-            if (ev)
+        if (ballot(rrem != (W)0))
+            if (rrem != (W)0)
                 found = evaluate(w, b);
-        }
         if (ballot(found)) {
             // where the child's frame starts: above this one, or, where it
             // might not fit, in the wavefront's worst-case area, if no other
@@ -619,39 +744,48 @@ struct LaneSearch {
                     }
                 }
             }
-            if (ballot(found && nb >= cap)) {
-                n_big += (unsigned)__builtin_popcountll(ballot(found && nb >= cap));
-                if (found && nb >= cap &&
-                    (uint32_t)(nb - cap + HE + (b - d - 1)) > big_cap) {
-                    fail_lane(kErrStack);  // a broken invariant: past the worst case
-                    found = false;
+            const uint64_t in_big = ballot(found && nb >= cap);
+            if (in_big) {
+                n_big += (unsigned)__builtin_popcountll(in_big);
+                const bool over = found && nb >= cap &&
+                                  (uint32_t)(nb - cap + HE + (b - d - 1)) > big_cap;
+                if (ballot(over)) {
+                    fail(kErrStack);  // a broken invariant: past the worst case
+                    found = found && !over;
                 }
             }
-            const int inc0 = inc;
+            const int size = d + 1;
+            uint64_t up = ballot(found && size > inc);
             if (found)
                 descend(w, b, nb);
-            uint64_t up = ballot(inc > inc0);
-            while (up) {  // (rare) tell the wavefront's other searches
+            while (up) {
                 const int l = ctz(up);
                 up &= up - 1;
-                const int li = rl(inst, l), lv = rl(inc, l);
-                if (inst == li && lv > inc)
-                    inc = lv;
+                const int sz = rl(size, l);
+                if (sz > inc)
+                    improve(l, sz);
             }
         }
         n_steps += 1;
-        if (ballot(fin))
-            finish_units();
     }
 
     // ---- work sharing inside the wavefront ----
 
-    // Idle lanes take the lowest open frame of busy lanes, one each: lane
-    // j-th idle from the j-th lane with a frame below its top.
+    // Idle lanes take the lowest open frame of busy lanes, one each, from
+    // the lanes whose lowest open frame is (nearly) the shallowest: a frame
+    // near the leaves is gone in a few steps.
     __device__ void steal() {
-        const bool is_i = t < 0, is_v = t >= 0 && lo_t < t;
-        const uint64_t im = ballot(is_i), vm = ballot(is_v);
-        const int ni = __builtin_popcountll(im), nv = __builtin_popcountll(vm);
+        const bool is_i = t < 0;
+        bool is_v = t >= 0 && lo_t < t;
+        const uint32_t depth = is_v ? (uint32_t)(d - t + lo_t) : 0xFFFFu;
+        const uint64_t im = ballot(is_i);
+        const int ni = __builtin_popcountll(im);
+        uint32_t most = wave_min(depth);
+        uint64_t vm = ballot(is_v && depth <= most);
+        for (int i = 0; i < kStealSpan && __builtin_popcountll(vm) < ni; ++i)
+            vm = ballot(is_v && depth <= ++most);
+        is_v = is_v && depth <= most;
+        const int nv = __builtin_popcountll(vm);
         const int n = ni < nv ? ni : nv;
         if (n == 0)
             return;
@@ -662,10 +796,8 @@ struct LaneSearch {
         const int vl = shfl_any(vj, ri), tl = shfl_any(ij, rv);
         const bool thief = is_i && ri < n, robbed = is_v && rv < n;
         int fb = shfl_any(lo_base, vl), ft = shfl_any(lo_t, vl);
-        const int vt = shfl_any(t, vl);
-        const int vinst = shfl_any(inst, vl), vinc = shfl_any(inc, vl);
-        const int vtarget = shfl_any(target, vl);
-        wave_sync_global();  // frames written by other lanes
+        const int vt = shfl_any(t, vl), vw = shfl_any(wlo, vl);
+        wave_sync();  // (entries written by other lanes)
         bool got = false;
         Hdr h;
         h.x = h.y = 0;
@@ -675,106 +807,159 @@ struct LaneSearch {
             if (ballot(look) == 0)
                 break;
             if (look) {
-                h = ld_hdr(at(vl, fb));
-                const int hb = (int)((h.y >> 16) & 0xFFu), hf = (int)(h.y >> 24);
-                if ((h.r != (W)0 || (hf & kUnm)) && !(reprune && hb <= vinc)) {
-                    got = true;
-                } else {
-                    fb = (hf & kBig) ? cap : fb + HE + (int)((h.x >> 16) & 0xFFu);
+                h = get_hdr(vl, fb, vw);
+                got = open_frame(h);
+                if (!got) {
+                    fb = next_frame(fb, h);
                     ft += 1;
                 }
             }
         }
-        // the victim's side: its lowest open frame is at or above the one taken
-        const int rb = shfl_any(fb, tl), rt = shfl_any(ft, tl), rg = shfl_any(got ? 1 : 0, tl);
+        // the victim's lowest open frame is above the one taken
+        const int rb = shfl_any(got ? next_frame(fb, h) : fb, tl);
+        const int rt = shfl_any(got ? ft + 1 : ft, tl);
         if (robbed) {
             lo_base = rb;
             lo_t = rt;
-            if (rg && pv && pbase == rb) {
-                c_r = (W)0;
-                c_y &= ~((uint32_t)kUnm << 24);
-            }
         }
         if (got) {
             Hdr e = h;
             e.r = (W)0;
             e.y &= ~((uint32_t)kUnm << 24);
-            st_hdr(at(vl, fb), e);  // nothing is left of it there
-            if (inst != vinst)
-                flush_lane();
-            inst = vinst;
-            inc = vinc;
-            target = vtarget;
-            rows = gadj + (size_t)inst * (NR * NB);
+            put_hdr(vl, fb, vw, e);  // nothing is left of it there
             K = (int)((h.x >> 16) & 0xFFu);
             start_frame((int)(h.x >> 24), h.y, h.r);
-            flags |= kDirty;
-            const uint32_t src = at(vl, fb + HE);
-            const uint32_t dst = at(lane, HE);
-            for (int k = 0; ballot(k < K) != 0; ++k) {
-                if (k < K) {
-                    const Cls<W> c = gget(src + (uint32_t)k * EB);
-                    if (k < kc)
-                        lput(lane, 0, k, c);
-                    else
-                        gput(dst + (uint32_t)k * EB, c);
-                }
+            wlo = HE + K > rc ? HE + K - rc : 0;
+            wslot = slot_of(wlo);
+            for (int k = 0; ballot(k < K) != 0; k += 4) {
+                Ent x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    x[i] = eget(vl, fb + HE + (k + i < K ? k + i : K - 1), vw);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k + i < K)
+                        eput(lane, HE + k + i, wlo, x[i]);
             }
-            for (int j = 0; ballot(j < d) != 0; j += 8)
-                if (j < d) {
-                    const v2u64 x = ld16((uint32_t)vl * stride + 2u * j);
-                    st16((uint32_t)lane * stride + 2u * j, x[0], x[1]);
-                }
+            for (int j = 0; ballot(j < d) != 0; j += 32) {
+                // (up to 32 pairs in flight; past d, within the map, anything)
+                v2u64 x[4];
+                const uint32_t top = map_bytes - 16u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    x[i] = *(glb_ptr<v2u64>)(wst + (uint32_t)vl * stride +
+                                             umin(2u * (uint32_t)j + 16u * i, top));
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (j + 8 * i < d)
+                        *(glb_ptr<v2u64>)(wst + (uint32_t)lane * stride + 2u * j + 16u * i) = x[i];
+            }
         }
         n_don += (unsigned)__builtin_popcountll(ballot(got));
-        wave_sync_global();
+        wave_sync();
     }
 
-    // The lane's only frame, from a header's fields (K is set).
+    // Whether a frame below a top still has work, and where the one above it
+    // starts.
+    __device__ bool open_frame(const Hdr &h) const {
+        return (h.r != (W)0 || ((h.y >> 24) & kUnm)) &&
+               !(reprune && (int)((h.y >> 16) & 0xFFu) <= inc);
+    }
+    __device__ int next_frame(int fb, const Hdr &h) const {
+        return ((h.y >> 24) & kBig) ? cap : fb + HE + (int)((h.x >> 16) & 0xFFu);
+    }
+
+    // The lane's only frame, from a header's fields (K and the ring are set
+    // by the caller).
     __device__ void start_frame(int fd, uint32_t y, const W &r) {
         t = 0;
-        base = pbase = 0;
+        base = pbase = bslot = 0;
         lo_t = lo_base = 0;
-        pv = false;
         d = fd;
         v = (int)(y & 0xFFu);
         sel = (int)((y >> 8) & 0xFFu);
         bound = (int)((y >> 16) & 0xFFu);
         rrem = r;
-        flags = ((int)(y >> 24) & kSaved) | kInLds | (r != (W)0 ? kRow : 0);
+        flags = ((int)(y >> 24) & kSaved) | (r != (W)0 ? kRow : 0);
     }
 
     // ---- work sharing between wavefronts ----
 
     __device__ void raise_flag(unsigned bits) {
+        if (lane == 0) {
+            if (bits & kFlagStop)
+                __hip_atomic_store(&P.g->stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < kRings; ++k)
+                __hip_atomic_fetch_or(&P.g->xcd[k].flag, bits, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __device__ void fail(unsigned code) {
         if (lane == 0)
-            raise_any(bits);
-    }
-    __device__ void raise_any(unsigned bits) {
-        if (bits & kFlagStop)
-            __hip_atomic_store(&P.g->stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int k = 0; k < kRings; ++k)
-            __hip_atomic_fetch_or(&P.g->xcd[k].flag, bits, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // A check failed in the lanes that call this (possibly few of them).
-    __device__ void fail_lane(unsigned code) {
-        __hip_atomic_store(&P.g->error, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        raise_any(kFlagStop);
+            __hip_atomic_store(&P.g->error, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_flag(kFlagStop);
+        stop = true;  // (this wavefront leaves at the end of the step)
     }
 
-    // A free slot in this XCD's ring, else in the next rings.
-    __device__ bool reserve(int &ring, unsigned long long &ticket) {
-        const unsigned long long mask = (unsigned long long)P.ring_slots - 1;
+    // The lane with the shallowest open frame below its top gives it away:
+    // the lane (-1: none), the frame and its header, as scalars.  The frame
+    // is not marked yet.
+    __device__ int pick_frame(int &fb, Hdr &h) {
+        for (int tries = 0; tries < 4; ++tries) {
+            const bool c = t >= 0 && lo_t < t;
+            const uint32_t key = wave_min(c ? ((uint32_t)(d - t + lo_t) << 8) | (uint32_t)lane
+                                            : ~0u);
+            if (key == ~0u || (int)(key >> 8) > P.donate_depth)
+                return -1;
+            const int l = (int)(key & 63u);
+            int ft = rl(lo_t, l);
+            const int lt = rl(t, l), lw = rl(wlo, l);
+            fb = rl(lo_base, l);
+            while (ft < lt) {
+                h = get_hdr(l, fb, lw);
+                h.x = sc(h.x);
+                h.y = sc(h.y);
+                h.r = sc(h.r);
+                if (open_frame(h))
+                    break;
+                fb = next_frame(fb, h);
+                ft += 1;
+            }
+            if (lane == l) {
+                lo_base = fb;
+                lo_t = ft;
+            }
+            if (ft < lt && (int)(h.x >> 24) <= P.donate_depth)
+                return l;
+        }
+        return -1;
+    }
+    // Nothing is left of lane l's frame fb.
+    __device__ void gave(int l, int fb, Hdr h) {
+        h.r = (W)0;
+        h.y &= ~((uint32_t)kUnm << 24);
+        const int lw = rl(wlo, l);
+        if (lane == l) {
+            lo_base = next_frame(fb, h);
+            lo_t += 1;
+        }
+        if (lane == 0)
+            put_hdr(l, fb, lw, h);
+        n_don += 1;
+    }
+
+    // A free slot in ring `from`, else in the next rings.
+    __device__ bool reserve(int from, int &ring, u64w &ticket) {
+        const u64w mask = (u64w)P.ring_slots - 1;
         int ok = 0, rr = 0;
-        unsigned long long tk = 0;
+        u64w tk = 0;
         if (lane == 0) {
             for (int k = 0; k < kRings && !ok; ++k) {
-                const int r = (my_ring + k) & (kRings - 1);
-                unsigned long long *sq = P.seq + (size_t)r * P.ring_slots;
+                const int r = (from + k) & (kRings - 1);
+                u64w *sq = P.seq + (size_t)r * P.ring_slots;
                 for (int tries = 0; tries < 4; ++tries) {
-                    const unsigned long long tl = ld_rlx(&P.g->ring[r].tail);
-                    const unsigned long long s = ld_rlx(&sq[tl & mask]);
+                    const u64w tl = ld_rlx(&P.g->ring[r].tail);
+                    const u64w s = ld_rlx(&sq[tl & mask]);
                     if (s == tl) {
                         if (cas64(&P.g->ring[r].tail, tl, tl + 1)) {
                             ok = 1;
@@ -794,43 +979,23 @@ struct LaneSearch {
         return ok != 0;
     }
 
-    // Lane l's lowest open frame below its top goes to the queue; false if
-    // it has none, or no slot is free.
-    __device__ bool donate(int l) {
-        int fb = rl(lo_base, l), ft = rl(lo_t, l);
-        const int lt = rl(t, l), linc = rl(inc, l);
+    // A frame to the queue; false if there is none, or no slot is free.
+    __device__ bool donate(int to) {
+        int fb = 0;
         Hdr h;
-        bool got = false;
-        while (ft < lt) {
-            h = ld_hdr(at(l, fb));
-            h.x = sc(h.x);
-            h.y = sc(h.y);
-            h.r = sc(h.r);
-            const int hb = (int)((h.y >> 16) & 0xFFu), hf = (int)(h.y >> 24);
-            if ((h.r != (W)0 || (hf & kUnm)) && !(reprune && hb <= linc)) {
-                got = true;
-                break;
-            }
-            fb = (hf & kBig) ? cap : fb + HE + (int)((h.x >> 16) & 0xFFu);
-            ft += 1;
-        }
-        if (lane == l) {
-            lo_base = fb;
-            lo_t = ft;
-        }
-        if (!got || (int)(h.x >> 24) > P.donate_depth)
+        const int l = pick_frame(fb, h);
+        if (l < 0)
             return false;
-        unsigned long long ticket;
+        u64w ticket;
         int ring;
-        if (!reserve(ring, ticket))
+        if (!reserve(to, ring, ticket))
             return false;
-        const unsigned long long mask = (unsigned long long)P.ring_slots - 1;
+        const u64w mask = (u64w)P.ring_slots - 1;
         const size_t idx = (size_t)ring * P.ring_slots + (size_t)(ticket & mask);
         uint8_t *slot = P.slots + idx * (size_t)P.slot_bytes;
-        const int fK = (int)((h.x >> 16) & 0xFFu), fd = (int)(h.x >> 24);
-        const int ji = rl(inst, l);
+        const int fK = (int)((h.x >> 16) & 0xFFu), fd = (int)(h.x >> 24), lw = rl(wlo, l);
         RecHdr<W> rh;
-        rh.inst = (uint32_t)ji;
+        rh.inst = (uint32_t)inst;
         rh.K = (uint8_t)fK;
         rh.d = (uint8_t)fd;
         rh.v = (uint8_t)(h.y & 0xFFu);
@@ -840,88 +1005,166 @@ struct LaneSearch {
         rh.lsel = rh.rsel = 0;
         rh.pad[0] = rh.pad[1] = rh.pad[2] = rh.pad[3] = 0;
         rh.rrem = h.r;
-        constexpr int HW = (int)(sizeof(RecHdr<W>) + 7) / 8;
-        if (lane == 0) {
-            unsigned long long ws[HW] = {};
-            __builtin_memcpy(ws, &rh, sizeof(rh));
-            for (int i = 0; i < HW; ++i)
-                st_agent((unsigned long long *)slot + i, ws[i]);
-        }
+        if (lane == 0)
+            *(RecHdr<W> *)slot = rh;
         // mapping (four pairs a word) and classes
-        unsigned long long *rmap = (unsigned long long *)(slot + rec_map_off<W>());
+        u64w *rmap = (u64w *)(slot + rec_map_off<W>());
         for (int i = lane; 4 * i < fd; i += 64)
-            st_agent(rmap + i, *(glb_ptr<unsigned long long>)(wst + (uint32_t)l * stride + 8u * i));
-        unsigned long long *rcls = (unsigned long long *)(slot + rec_cls_off<W>());
-        const uint32_t src = at(l, fb + HE);
-        for (int i = lane; i < fK * (EB / 8); i += 64)
-            st_agent(rcls + i, *(glb_ptr<unsigned long long>)(wst + src + 8u * i));
-        if (lane == 0) {
-            h.r = (W)0;
-            h.y &= ~((uint32_t)kUnm << 24);
-            st_hdr(at(l, fb), h);  // nothing is left of it here
-            a_add_rlx(&P.open[ji], 1);
+            rmap[i] = *(glb_ptr<u64w>)(wst + (uint32_t)l * stride + 8u * i);
+        u64w *rcls = (u64w *)(slot + rec_cls_off<W>());
+        for (int i = lane; i < fK; i += 64) {
+            const Ent x = eget(l, fb + HE + i, lw);
+#pragma unroll
+            for (int q = 0; q < EW; ++q)
+                rcls[(size_t)i * EW + q] = x.w[q];
+        }
+        gave(l, fb, h);
+        if (lane == 0) {  // the record is a unit of its own
+            a_add_rlx(&P.open[inst], 1);
             a_add_rlx(&P.g->open_total, 1);
         }
-        if (lane == l && pv && pbase == fb) {
-            c_r = (W)0;
-            c_y &= ~((uint32_t)kUnm << 24);
-        }
-        // every word of the record has been written before its sequence
-        // number says so
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
+        // every word of the record has been written, and its unit counted,
+        // before its sequence number says so (at agent scope: its reader may
+        // sit behind another L2)
         if (lane == 0)
-            st_rlx(&P.seq[idx], ticket + 1);
-        wave_sync_global();
-        n_don += 1;
+            st_rel(&P.seq[idx], ticket + 1);
+        wave_sync();
         return true;
     }
 
-    // Lane l works on instance i from now on (per-lane values; uniform i).
-    __device__ void enter(int i) {
-        if (inst != i)
-            flush_lane();
-        const DevInst di = P.inst[i];
-        inst = i;
-        target = (int)di.target;
-        rows = gadj + (size_t)i * (NR * NB);
-        inc = 0;
-        set_inc(read_inc(di, i));
+    // A frame to the waiting wavefront w of the workgroup: its classes and
+    // mapping into lane 0 of that wavefront's stacks, its header into the
+    // box.
+    __device__ void feed(unsigned hungry) {
+        wave_sync();
+        int fb = 0;
+        Hdr h;
+        const int l = pick_frame(fb, h);
+        if (l < 0)
+            return;
+        const int w = (int)ctz(hungry);
+        unsigned old = 0;
+        if (lane == 0)
+            old = __hip_atomic_fetch_and(&T.hungry, ~(1u << w), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (!((unsigned)rl((int)old, 0) & (1u << w)))
+            return;  // another wavefront serves it, or it found work
+        const int fK = (int)((h.x >> 16) & 0xFFu), fd = (int)(h.x >> 24), lw = rl(wlo, l);
+        const glb_ptr<char> ws = wst + (long long)(w - wv) * P.hstack_stride;
+        for (int i = lane; 4 * i < fd; i += 64)
+            *(glb_ptr<u64w>)(ws + 8u * i) = *(glb_ptr<u64w>)(wst + (uint32_t)l * stride + 8u * i);
+        const uint32_t dst = at(0, HE);
+        for (int i = lane; i < fK; i += 64) {
+            const Ent x = eget(l, fb + HE + i, lw);
+#pragma unroll
+            for (int q = 0; q < EW; ++q)
+                *(glb_ptr<u64w>)(ws + dst + (uint32_t)i * EB + 8u * q) = x.w[q];
+        }
+        if (lane == 0) {
+            T.box[w][0] = (u64w)h.x | ((u64w)h.y << 32);
+            T.box[w][1] = (u64w)(uint32_t)unit;
+            __hip_atomic_fetch_add(&T.ref[unit], 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int q = 0; q < (NB + 63) / 64; ++q)
+                T.box[w][2 + q] = word64(h.r, q);
+        }
+        gave(l, fb, h);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane == 0)
+            st_wg(&T.full[w], 1u);
     }
-    // The incumbent, or 255 where the instance needs no more search.
-    __device__ int read_inc(const DevInst &di, int i) const {
-        int g = ld_rlx(&P.inc[di.inc_slot]);
-        if (di.twin >= 0 && ld_rlx(&P.open[di.twin]) == 0 && !ld_rlx(&P.dead[di.twin]))
-            g = 255;  // the twin's search already finished
-        if (di.dead_on && ld_rlx(&P.dead[i]))
-            g = 255;  // given up as a dead end
-        return g;
+    // The frame that a sibling has put into this wavefront's stack.
+    __device__ void accept() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const u64w a = rl_ull(T.box[wv][0], 0);
+        const int u = (int)rl_ull(T.box[wv][1], 0);
+        uint64_t rw[4];
+#pragma unroll
+        for (int q = 0; q < (NB + 63) / 64; ++q)
+            rw[q] = rl_ull(T.box[wv][2 + q], 0);
+        if (lane == 0)
+            st_wg(&T.full[wv], 0u);
+        unit = u;
+        enter(rl(ld_wg(&T.inst[u]), 0));
+        set_inc(rl(ld_wg(&T.inc[u]), 0));
+        begin(0, (uint32_t)a, (uint32_t)(a >> 32), from_words<W>(rw));
+        n_pops += 1;
     }
-    // One more unit of instance i arrived: if the wavefront already works on
-    // it, the two are one from now on.
-    __device__ void merge_unit(int i) {
-        if (ballot(t >= 0 && inst == i) != 0 && lane == 0) {
-            a_add_rlx(&P.open[i], -1);
-            a_add_rlx(&P.g->open_total, -1);
+    // Lane l starts on a frame of the instance whose classes and mapping are
+    // in its part in HBM.
+    __device__ void begin(int l, uint32_t x, uint32_t y, const W &r) {
+        if (lane == l) {
+            K = (int)((x >> 16) & 0xFFu);
+            start_frame((int)(x >> 24), y, r);
+            wlo = HE + K;
+            wslot = slot_of(wlo);
+            if (bound <= inc) {
+                rrem = (W)0;
+                flags = 0;
+            }
         }
     }
 
-    // Take a queued node into lane l: from this XCD's ring, else from one
+    // A unit of instance i came from outside the workgroup.
+    __device__ void new_unit(int i) {
+        int u = 0;
+        if (lane == 0) {
+            // (one of 16 is free: each taken one has a wavefront on it)
+            for (u = wv;; u = (u + 1) & 15) {
+                unsigned want = 0;
+                if (__hip_atomic_compare_exchange_strong(&T.ref[u], &want, 2u, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_WORKGROUP))
+                    break;
+            }
+        }
+        unit = rl(u, 0);
+        enter(i);
+        set_inc(read_inc());
+        if (lane == 0) {
+            st_wg(&T.inst[unit], i);
+            st_wg(&T.inc[unit], inc);
+            st_wg(&T.seen[unit], (unsigned)now_ticks());
+        }
+    }
+    // The wavefront works on instance i from now on.
+    __device__ void enter(int i) {
+        const DevInst di = P.inst[i];
+        inst = i;
+        target = sc((int)di.target);
+        inc_slot = sc((int)di.inc_slot);
+        twin = sc((int)di.twin);
+        dead_on = sc((int)di.dead_on);
+        grow = (const W *)P.adj + (size_t)i * (NR * NB);
+        if constexpr (LROWS) {
+            if (rows_inst != i) {
+                for (int q = lane; q < NR * arows; q += 64)
+                    lrow[q] = grow[(q / arows) * NB + q % arows];
+                rows_inst = i;
+                wave_sync();
+            }
+        }
+        inc = 0;
+    }
+
+    // Take a queued node into lane 0: from this XCD's ring, else from one
     // other ring, a different one on each call.
-    __device__ bool take_record(int l) {
-        const unsigned long long mask = (unsigned long long)P.ring_slots - 1;
+    __device__ bool take_record() {
+        const int l = 0;
+        const u64w mask = (u64w)P.ring_slots - 1;
         int ok = 0, rr = 0;
-        unsigned long long hd = 0;
+        u64w hd = 0;
         if (lane == 0) {
             steal_from = (steal_from + 1) & (kRings - 1);
             if (steal_from == my_ring)
                 steal_from = (steal_from + 1) & (kRings - 1);
             for (int k = 0; k < 2 && !ok; ++k) {
                 const int r = k == 0 ? my_ring : steal_from;
-                unsigned long long *sq = P.seq + (size_t)r * P.ring_slots;
+                u64w *sq = P.seq + (size_t)r * P.ring_slots;
                 for (int tries = 0; tries < 4; ++tries) {
-                    const unsigned long long h = ld_rlx(&P.g->ring[r].head);
-                    const unsigned long long s = ld_rlx(&sq[h & mask]);
+                    const u64w h = ld_rlx(&P.g->ring[r].head);
+                    const u64w s = ld_rlx(&sq[h & mask]);
                     if (s == h + 1) {
                         if (cas64(&P.g->ring[r].head, h, h + 1)) {
                             ok = 1;
@@ -939,194 +1182,216 @@ struct LaneSearch {
         ok = rl(ok, 0);
         if (!ok)
             return false;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         hd = rl_ull(hd, 0);
         const int ring = rl(rr, 0);
         const size_t idx = (size_t)ring * P.ring_slots + (size_t)(hd & mask);
-        const uint8_t *slot = P.slots + idx * (size_t)P.slot_bytes;
-        constexpr int HW = (int)(sizeof(RecHdr<W>) + 7) / 8;
-        unsigned long long ws[HW];
-        for (int i = 0; i < HW; ++i)
-            ws[i] = ld_agent((const unsigned long long *)slot + i);
-        RecHdr<W> rh;
-        __builtin_memcpy(&rh, ws, sizeof(rh));
+        uint8_t *slot = P.slots + idx * (size_t)P.slot_bytes;
+        const RecHdr<W> rh = *(const RecHdr<W> *)slot;
         const int ri = sc((int)rh.inst);
         const int rK = sc((int)rh.K), rd = sc((int)rh.d);
         const uint32_t y = sc((uint32_t)rh.v | ((uint32_t)rh.sel << 8) |
                               ((uint32_t)rh.bound << 16) | ((uint32_t)rh.flags << 24));
         const W rr_ = sc((W)rh.rrem);
         // the record's words go straight to lane l's stack
-        const unsigned long long *rmap = (const unsigned long long *)(slot + rec_map_off<W>());
+        u64w *rmap = (u64w *)(slot + rec_map_off<W>());
         for (int i = lane; 4 * i < rd; i += 64)
-            *(glb_ptr<unsigned long long>)(wst + (uint32_t)l * stride + 8u * i) =
-                ld_agent(rmap + i);
-        const unsigned long long *rcls = (const unsigned long long *)(slot + rec_cls_off<W>());
+            *(glb_ptr<u64w>)(wst + (uint32_t)l * stride + 8u * i) = rmap[i];
+        u64w *rcls = (u64w *)(slot + rec_cls_off<W>());
         const uint32_t dst = at(l, HE);
-        for (int i = lane; i < rK * (EB / 8); i += 64)
-            *(glb_ptr<unsigned long long>)(wst + dst + 8u * i) = ld_agent(rcls + i);
+        for (int i = lane; i < rK * EW; i += 64)
+            *(glb_ptr<u64w>)(wst + dst + 8u * i) = rcls[i];
         // every lane's loads of the slot have returned before it is handed back
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         if (lane == 0)
-            st_rlx(&P.seq[idx], hd + (unsigned long long)P.ring_slots);
-        wave_sync_global();
-        merge_unit(ri);
-        if (lane == l) {
-            enter(ri);
-            K = rK;
-            start_frame(rd, y, rr_);
-            flags &= ~kInLds;  // (all of it is in HBM)
-            if (bound <= inc) {
-                rrem = (W)0;
-                flags = 0;
-            }
+            st_rlx(&P.seq[idx], hd + (u64w)P.ring_slots);
+        wave_sync();
+        if (ri >= P.count || rK > P.frames || rd >= P.frames) {
+            fail(kErrRecord);  // (a broken invariant: no such frame)
+            return false;
         }
+        new_unit(ri);
+        begin(l, ((uint32_t)rK << 16) | ((uint32_t)rd << 24), y, rr_);
         n_pops += 1;
         return true;
     }
 
-    // The next unstarted instances, one per idle lane (their work units were
-    // counted by the reset): several at a time while there are many more
-    // than wavefronts.
-    __device__ bool claim_instances() {
+    // The next unstarted instance (its work unit was counted by the reset).
+    __device__ bool claim_instance() {
         if (!roots_left)
             return false;
-        const uint64_t im = ballot(t < 0);
-        int first = 0, n = 0;
+        int i = -1;
         if (lane == 0) {
             const unsigned nx = ld_rlx(&P.g->next_inst);
             if (nx < (unsigned)P.count) {
-                const unsigned left = (unsigned)P.count - nx;
-                unsigned want = left / (2u * gridDim.x * (blockDim.x >> 6));
-                const unsigned room = (unsigned)__builtin_popcountll(im);
-                want = want < 1u ? 1u : want > room ? room : want;
-                if (P.single_wave)
-                    want = 1;
-                const unsigned x = a_addu(&P.g->next_inst, want);
-                if (x < (unsigned)P.count) {
-                    first = (int)x;
-                    n = (int)((unsigned)P.count - x < want ? (unsigned)P.count - x : want);
-                }
+                const unsigned x = a_addu(&P.g->next_inst, 1u);
+                if (x < (unsigned)P.count)
+                    i = (int)x;
             }
         }
-        first = rl(first, 0);
-        n = rl(n, 0);
-        if (n == 0) {
+        i = rl(i, 0);
+        if (i < 0) {
             roots_left = false;
             return false;
         }
-        const int r = mbcnt(im);
-        if (t < 0 && r < n) {
-            const int i = first + r;
-            enter(i);
-            const DevInst di = P.inst[i];
-            const Cls<W> *rc = (const Cls<W> *)P.rootcls + di.cls_off;
-            const uint32_t dst = at(lane, HE);
-            K = (int)di.K0;
-            int sum = 0;
-            for (int k = 0; ballot(k < K) != 0; ++k) {
-                if (k < K) {
-                    const Cls<W> c = ld_cls(rc + k);
-                    if (k < kc)
-                        lput(lane, 0, k, c);
-                    else
-                        gput(dst + (uint32_t)k * EB, c);
-                    const int nl = popc(c.L), nr = popc(c.R);
-                    sum += nl < nr ? nl : nr;
-                }
-            }
+        const DevInst di = P.inst[i];
+        const Cls<W> *rcl = (const Cls<W> *)P.rootcls + sc((int)di.cls_off);
+        const int k0 = sc((int)di.K0);
+        int sum = 0;
+        for (int k = lane; k < k0; k += 64) {
+            const Cls<W> c = ld_cls(rcl + k);
+            hput(at(0, HE + k), pack(c));
+            const int nl = popc(c.L), nr = popc(c.R);
+            sum += nl < nr ? nl : nr;
+        }
+        const int b = wave_sum(sum);
+        wave_sync();
+        new_unit(i);
+        begin(0, (uint32_t)k0 << 16, (uint32_t)b << 16, (W)0);
+        if (lane == 0) {
             c_unm += 1;  // the root
-            start_frame(0, (uint32_t)sum << 16, (W)0);
-            flags = (K == 0 || sum <= inc) ? 0 : kSel | kDirty | kInLds;
+            flags = (k0 == 0 || b <= inc) ? 0 : kSel;
         }
         return true;
     }
 
-    // Lanes whose last frame ended: a unit of the wavefront ends with the
-    // last lane on its instance.
-    __device__ void finish_units() {
-        uint64_t fm = ballot(fin);
-        while (fm) {
-            const int ji = rl(inst, ctz(fm));
-            fm &= ~ballot(inst == ji);
-            if (ballot(t >= 0 && inst == ji) == 0) {
-                if (P.node_limit > 0)
-                    flush_nodes();
-                if (lane == 0 && !stop) {
-                    const int r = a_add_rlx(&P.open[ji], -1);
-                    if (r == 1)
-                        __hip_atomic_store(&P.t_proof[ji], now_ticks(), __ATOMIC_RELAXED,
+    // No lane has work left.  The last wavefront to leave a unit ends it.
+    __device__ void finish_unit() {
+        const u64w mine = count_nodes();
+        if (lane == 0) {
+            __hip_atomic_fetch_add(&T.nodes[unit], mine, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (__hip_atomic_fetch_add(&T.ref[unit], ~0u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP) == 2u) {
+                add_nodes(__hip_atomic_exchange(&T.nodes[unit], 0ull, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP));
+                if (!stop) {
+                    if (a_add_rlx(&P.open[inst], -1) == 1)
+                        __hip_atomic_store(&P.t_proof[inst], now_ticks(), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                     if (a_add_rlx(&P.g->open_total, -1) == 1)
-                        raise_any(kFlagDone);
+                        raise_flag(kFlagDone);
                 }
+                st_wg(&T.ref[unit], 0u);
             }
         }
-        fin = false;
+        unit = -1;
     }
 
     // ---- counts ----
 
-    // The lane's nodes since its last flush, to its instance's count.
-    __device__ void flush_lane() {
-        if (c_child + c_unm != 0)
-            a_add64(&P.nodes[inst], (unsigned long long)c_child + c_unm);
-        n_child += c_child;
-        n_ncls += c_ncls;
-        n_pushed += c_pushed;
+    // The nodes counted since the last call.
+    __device__ u64w count_nodes() {
+        const u64w child = lanes_total(c_child), sum = child + lanes_total(c_unm);
+        n_child += child;
+        n_ncls += lanes_total(c_ncls);
+        n_pushed += lanes_total(c_pushed);
         c_child = c_unm = c_ncls = c_pushed = 0;
+        return sum;
     }
-    __device__ void flush_nodes() {
-        const unsigned long long np = (unsigned long long)c_child + c_unm;
-        const unsigned long long sum = lanes_total(np);
-        flush_lane();
-        if (lane == 0 && sum && P.node_limit > 0) {
-            const unsigned long long tot = a_add64(&P.g->node_total, sum) + sum;
+    // (lane 0) Nodes to the instance's count.
+    __device__ void add_nodes(u64w n) {
+        if (n == 0)
+            return;
+        a_add64(&P.nodes[inst], n);
+        if (P.node_limit > 0) {
+            const u64w tot = a_add64(&P.g->node_total, n) + n;
             if ((long long)tot > P.node_limit)
-                raise_any(kFlagStop);
+                raise_flag(kFlagStop);
         }
     }
-    DEV unsigned long long lanes_total(unsigned long long x) {
-        // (24-bit pieces: 64 of them sum below 2^31)
-        return (unsigned long long)(unsigned)wave_sum((int)(x & 0xFFFFFFu)) +
-               ((unsigned long long)(unsigned)wave_sum((int)((x >> 24) & 0xFFFFFFu)) << 24) +
-               ((unsigned long long)(unsigned)wave_sum((int)((x >> 48) & 0xFFFFu)) << 48);
+    __device__ void flush_nodes() {
+        const u64w n = count_nodes();
+        if (lane == 0)
+            add_nodes(n);
+    }
+    DEV u64w lanes_total(uint32_t x) {
+        // (16-bit pieces: 64 of them sum below 2^31)
+        return (u64w)(unsigned)wave_sum((int)(x & 0xFFFFu)) +
+               ((u64w)(unsigned)wave_sum((int)(x >> 16)) << 16);
     }
 
     // Dead-end forecast (paper Sec. IV.A), as in the other kernels.
     __device__ void forecast_dead_ends() {
-        if (t >= 0 && P.inst[inst].dead_on) {
-            const unsigned long long n = ld_rlx(&P.nodes[inst]);
-            const unsigned long long b = ld_rlx(&P.best_nodes[inst]);
-            const unsigned long long since = n > b ? n - b : 0ull;
-            unsigned long long thr = (unsigned long long)P.dead_abs;
-            if (P.dead_rel > 0 && (unsigned long long)P.dead_rel * b > thr)
-                thr = (unsigned long long)P.dead_rel * b;
+        if (!dead_on)
+            return;
+        int give_up = 0;
+        if (lane == 0) {
+            const u64w n = ld_rlx(&P.nodes[inst]);
+            const u64w b = ld_rlx(&P.best_nodes[inst]);
+            const u64w since = n > b ? n - b : 0ull;
+            u64w thr = (u64w)P.dead_abs;
+            if (P.dead_rel > 0 && (u64w)P.dead_rel * b > thr)
+                thr = (u64w)P.dead_rel * b;
             if (since > thr) {
                 st_rlx(&P.dead[inst], 1);
-                inc = 255;
+                give_up = 1;
             }
         }
+        if (rl(give_up, 0))
+            inc = 255;
     }
 
-    // Periodic: refresh incumbents, honour limits, keep the queue stocked.
+    // True once every P.check_ticks for one of the workgroup's wavefronts.
+    __device__ bool my_turn(unsigned *last) {
+        int mine = 0;
+        if (lane == 0) {
+            unsigned old = ld_wg(last);
+            const unsigned now = (unsigned)now_ticks();
+            mine = now - old >= (unsigned)P.check_ticks &&
+                   __hip_atomic_compare_exchange_strong(last, &old, now, __ATOMIC_RELAXED,
+                                                        __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        return rl(mine, 0) != 0;
+    }
+
+    // Periodic.  What all XCDs share is looked at by one wavefront of the
+    // workgroup at a time: lines that thousands of wavefronts read and raise
+    // cost tens of microseconds each.
     __device__ void check() {
         since_check = 0;
-        unsigned fl = 0;
-        unsigned long long hd = 0, tl = 0;
+        if (rl((int)ld_wg(&T.done), 0)) {
+            stop = true;
+            return;
+        }
+        set_inc(rl(ld_wg(&T.inc[unit]), 0));
+        if (my_turn(&T.seen[unit])) {
+            set_inc(read_inc());
+            if (lane == 0)
+                __hip_atomic_fetch_max(&T.inc[unit], inc, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        if (P.node_limit > 0 || P.dead_abs > 0 ||
+            ballot((c_child | c_unm | c_ncls | c_pushed) > (1u << 30)))
+            flush_nodes();
+        if (P.dead_abs > 0)
+            forecast_dead_ends();
+        if (my_turn(&T.looked))
+            look_out();
+    }
+
+    // Limits, and frames for the rings: while workgroups of this XCD, or of
+    // another one (a different one each time), are idle and their ring holds
+    // fewer.
+    __device__ void look_out() {
         const bool may_donate = !P.single_wave && P.donate_low >= 0;
-        if (lane == 0) {
-            fl = ld_rlx(&P.g->xcd[my_ring].flag);
-            if (may_donate) {
-                tl = ld_rlx(&P.g->ring[my_ring].tail);
-                hd = ld_rlx(&P.g->ring[my_ring].head);
-            }
+        other = (other + 1) & (kRings - 1);
+        if (other == my_ring)
+            other = (other + 1) & (kRings - 1);
+        u64w x = 0;
+        {
+            // six lines in one round trip
+            const int q = lane < 3 ? my_ring : other, f = lane < 3 ? lane : lane - 3;
+            u64w *at = f == 0   ? (u64w *)&P.g->xcd[q]
+                       : f == 1 ? (u64w *)&P.g->ring[q].tail
+                                : (u64w *)&P.g->ring[q].head;
+            if (lane < 6)
+                x = ld_rlx(at);
         }
-        if (t >= 0) {
-            const DevInst di = P.inst[inst];
-            set_inc(read_inc(di, inst));
-        }
-        if (rl(fl, 0)) {
+        const u64w ctl = rl_ull(x, 0);
+        if ((unsigned)ctl) {
             stop = true;
             return;
         }
@@ -1135,140 +1400,211 @@ struct LaneSearch {
             stop = true;
             return;
         }
-        if (P.node_limit > 0 || P.dead_abs > 0 ||
-            ballot((c_child | c_unm | c_ncls | c_pushed) > (1u << 30)))
-            flush_nodes();
-        if (P.dead_abs > 0)
-            forecast_dead_ends();
-        if (may_donate) {
-            long long waiting = (long long)(rl_ull(tl, 0) - rl_ull(hd, 0));
-            if (waiting < P.donate_low) {
-                wave_sync_global();
-                // the shallowest frames first
-                for (int tries = 0; tries < 4 && waiting < P.donate_low; ++tries) {
-                    const bool c = t >= 0 && lo_t < t;
-                    const uint32_t key =
-                        wave_min(c ? ((uint32_t)(d - t + lo_t) << 8) | (uint32_t)lane : ~0u);
-                    if (key == ~0u)
-                        break;
-                    if (donate((int)(key & 63u)))
-                        waiting += 1;
-                }
-            }
-        }
+        if (!may_donate)
+            return;
+        const long long waiting = (long long)(rl_ull(x, 1) - rl_ull(x, 2));
+        const long long waiting_o = (long long)(rl_ull(x, 4) - rl_ull(x, 5));
+        const int idle = (int)(ctl >> 32), idle_o = (int)(rl_ull(x, 3) >> 32);
+        int want = idle > waiting ? (int)(idle - waiting) : 0;
+        if (waiting < P.donate_low && want < 1)
+            want = 1;
+        const bool want_o = idle_o > waiting_o;
+        if (want == 0 && !want_o)
+            return;
+        wave_sync();
+        bool more = true;
+        // (one each: four or sixteen at a time were no faster, the L2-wide
+        // releases cost more than the earlier start gains)
+        for (int i = 0; i < 2 && more; ++i)
+            if (i == 0 ? want > 0 : want_o)
+                more = donate(i == 0 ? my_ring : other);
     }
 
-    // Work for a wavefront with idle lanes; false if none was found.
-    __device__ bool refill() {
-        if (!P.single_wave) {
-            const uint64_t im = ballot(t < 0);
-            if (take_record(ctz(im)))
-                return true;
-        } else if (ballot(t >= 0) != 0) {
-            return false;  // one search only: the sequential order
+    // An idle wavefront takes the next instance, or waits for a sibling's
+    // frame.  The first of the idle siblings looks at the rings meanwhile,
+    // seldom while others of the workgroup are busy (they will feed it).
+    // False: the search is over.
+    __device__ void count_idle(unsigned idle) {
+        // (by the wavefront that looks at the rings: one at a time)
+        if (lane == 0 && ld_wg(&T.idle) != idle) {
+            st_wg(&T.idle, idle);
+            a_add_rlx(&P.g->xcd[my_ring].idle, idle ? 1 : -1);
         }
-        return claim_instances();
+    }
+    __device__ bool wait_work(bool share, bool claim) {
+        // (a sibling may write this wavefront's stack from here on: its own
+        // stores there have completed)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        const u64w t_sleep = now_ticks();
+        const unsigned bit = 1u << wv, all = (2u << ((blockDim.x >> 6) - 1u)) - 1u;
+        unsigned gap = 1, left = 1;
+        bool listed = false, fed = false, first = true;
+        for (;;) {
+            if (first && !claim) {
+                first = false;
+                continue;
+            }
+            if (!first) {
+                if (share && !listed) {
+                    if (lane == 0)
+                        __hip_atomic_fetch_or(&T.hungry, bit, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+                    listed = true;
+                }
+                __builtin_amdgcn_s_sleep(8);
+                if (rl((int)ld_wg(&T.full[wv]), 0)) {
+                    fed = true;
+                    break;
+                }
+                const bool over = rl((int)ld_wg(&T.done), 0) != 0;
+                const unsigned hungry = (unsigned)rl((int)ld_wg(&T.hungry), 0);
+                if (left != 0)
+                    left -= 1;
+                if (share && hungry == all && left > gap)
+                    left = gap;
+                if (!over && (left != 0 || (share && (hungry & (bit - 1u)) != 0)))
+                    continue;
+                const bool alone = !share || hungry == all;  // nobody here can feed it
+                if (listed) {
+                    unsigned old = 0;
+                    if (lane == 0)
+                        old = __hip_atomic_fetch_and(&T.hungry, ~bit, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+                    listed = false;
+                    if (!((unsigned)rl((int)old, 0) & bit)) {
+                        // a sibling has taken the bit off: its frame is on its way
+                        while (!rl((int)ld_wg(&T.full[wv]), 0))
+                            __builtin_amdgcn_s_sleep(2);
+                        fed = true;
+                        break;
+                    }
+                }
+                if (over)
+                    break;
+                if (share && alone)
+                    count_idle(1);
+                unsigned fl = 0;
+                if (lane == 0)
+                    fl = ld_rlx(&P.g->xcd[my_ring].flag);
+                if (rl((int)fl, 0))
+                    break;  // stopped, or no work is left anywhere
+                if (now_ticks() - t_start > P.limit_ticks) {
+                    raise_flag(kFlagStop);
+                    break;
+                }
+                if (!P.single_wave && take_record())
+                    break;
+                gap = gap < (unsigned)P.backoff_max ? 2 * gap : gap;
+                left = alone ? gap : kFedGap * gap;
+            }
+            first = false;
+            if (claim_instance())
+                break;
+        }
+        if (fed)
+            accept();
+        else if (unit >= 0)
+            count_idle(0);
+        n_sleep += now_ticks() - t_sleep;
+        return unit >= 0;
     }
 
     __device__ void main_loop() {
         t_start = now_ticks();
         if (lane == 0)
             a_min64(&P.g->t0, t_start);
-        const int check_interval = sc(P.check_interval);
         const bool share = !P.single_wave && P.donate_low >= 0;
-        int backoff = 0, look = 0, look_gap = 8, since_steal = 0;
-        unsigned long long t_busy0 = 0;
-        bool busy = false;
+        const int check_interval = sc(P.check_interval);
+        int since_steal = 0, since_feed = 0;
+        u64w t_busy0 = t_start;
+        // the first instances go to the first wavefronts of all workgroups
+        bool claim = (unsigned)wv * gridDim.x < (unsigned)P.count;
         for (;;) {
-            uint64_t am = ballot(t >= 0);
-            if (am != ~0ull) {
+            const uint64_t am = ballot(t >= 0);
+            if (am == 0) {
+                if (unit >= 0) {
+                    finish_unit();
+                    n_busy += now_ticks() - t_busy0;
+                }
+                if (!wait_work(share, claim))
+                    break;
+                claim = true;
+                t_busy0 = now_ticks();
+            } else if (am != ~0ull && share) {
                 const int idle = 64 - __builtin_popcountll(am);
-                if (share && am != 0 && (idle >= 8 || ++since_steal >= 4)) {
+                if (idle >= kIdleLanes || ++since_steal >= kStealSteps) {
                     since_steal = 0;
                     steal();
-                    am = ballot(t >= 0);
                 }
-                // a wavefront with no work at all, or (now and then: a failed
-                // look costs a queue round trip) with few lanes busy, looks
-                // outside
-                if (am == 0 || (__builtin_popcountll(am) <= 32 && ++look >= look_gap)) {
-                    look = 0;
-                    if (refill())
-                        look_gap = 8;
-                    else if (am != 0)
-                        look_gap = look_gap < 512 ? 2 * look_gap : 512;
-                }
-            }
-            if (ballot(t >= 0) == 0) {
-                if (busy) {
-                    n_busy += now_ticks() - t_busy0;
-                    busy = false;
-                }
-                unsigned fl = 0;
-                if (lane == 0)
-                    fl = ld_rlx(&P.g->xcd[my_ring].flag);
-                if (rl(fl, 0))
-                    break;  // stopped, or no work is left anywhere
-                if (now_ticks() - t_start > P.limit_ticks) {
-                    raise_flag(kFlagStop);
-                    break;
-                }
-                const int bmax = P.backoff_max;
-                backoff = backoff ? (2 * backoff < bmax ? 2 * backoff : bmax) : 1;
-                const unsigned long long t_sleep = now_ticks();
-                for (int i = 0; i < backoff; ++i)
-                    __builtin_amdgcn_s_sleep(127);
-                n_sleep += now_ticks() - t_sleep;
-                continue;
-            }
-            backoff = 0;
-            if (!busy) {
-                t_busy0 = now_ticks();
-                busy = true;
             }
             step();
             if (stop)
                 break;
+            if (share && ++since_feed >= kFeedSteps &&
+                (__builtin_popcountll(ballot(t >= 0)) >= kFeedRich || since_feed >= kFeedAnyway)) {
+                const unsigned hungry = (unsigned)rl((int)ld_wg(&T.hungry), 0);
+                if (hungry) {
+                    feed(hungry);
+                    since_feed = 0;
+                }
+            }
             if (++since_check >= check_interval) {
                 check();
                 if (stop)
                     break;
             }
         }
-        if (busy)
+        if (lane == 0)
+            st_wg(&T.done, 1u);
+        if (unit >= 0) {
             n_busy += now_ticks() - t_busy0;
-        flush_lane();
-        const unsigned long long child = lanes_total(n_child), ncls = lanes_total(n_ncls),
-                                 pushed = lanes_total(n_pushed);
+            const u64w n = count_nodes();
+            if (lane == 0)
+                add_nodes(n + __hip_atomic_exchange(&T.nodes[unit], 0ull, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP));
+        }
         const int mu = (int)~wave_min(~(uint32_t)max_used);
         if (lane == 0) {
             a_add64(&P.g->batches, n_steps);
-            a_add64(&P.g->children, child);
-            a_add64(&P.g->lane_slots, child);
+            a_add64(&P.g->children, n_child);
+            a_add64(&P.g->lane_slots, n_child);
             a_add64(&P.g->donations, n_don);
             a_add64(&P.g->pops, n_pops);
             a_add64(&P.g->busy_ticks, n_busy);
             a_add64(&P.g->hbm_frames, n_big);
-            a_add64(&P.g->pushed_classes, pushed);
+            a_add64(&P.g->pushed_classes, n_pushed);
             a_add64(&P.g->sleep_ticks, n_sleep);
-            a_add64(&P.g->node_classes, ncls);
+            a_add64(&P.g->node_classes, n_ncls);
             __hip_atomic_fetch_max(&P.g->max_stack, mu, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 };
 
+// Up to 64 vertices a workgroup may hold a CU's 16 wavefronts (128 VGPRs);
+// wider rows take more registers, and workgroups of at most 8.
 template <typename W, bool DIR>
-__global__ void __launch_bounds__(256, 2) mcs_lane_kernel(SearchParams Pk) {
+__global__ void __launch_bounds__(sizeof(W) <= 8 ? 1024 : 512) mcs_lane_kernel(SearchParams Pk) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ SearchParams P;
-    if (threadIdx.x == 0)
-        P = Pk;
+    __shared__ Team T;
+    const KernArgs &P = *(const KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    if (threadIdx.x == 0) {
+        T.hungry = 0;
+        T.done = 0;
+        T.looked = 0;
+        T.idle = 0;
+    }
+    if (threadIdx.x < 16) {
+        T.full[threadIdx.x] = 0;
+        T.ref[threadIdx.x] = 0;
+        T.nodes[threadIdx.x] = 0;
+    }
     __syncthreads();
-    const int wv = (int)threadIdx.x >> 6;
+    const int wv = sc((int)threadIdx.x >> 6);
     if (Pk.single_wave && (blockIdx.x != 0 || wv != 0))
         return;
-    LaneSearch<W, DIR> s(P, (lds_ptr<char>)smem + (size_t)sc(wv) * (size_t)Pk.lds_per_wave,
+    LaneSearch<W, DIR> s(P, T, (lds_ptr<char>)smem + (size_t)wv * (size_t)Pk.lds_per_wave, wv,
                          sc((int)(blockIdx.x * (blockDim.x >> 6)) + wv));
     s.main_loop();
 }

@@ -40,7 +40,8 @@ constexpr unsigned kFlagDone = 2;  // no work unit is left
 
 struct XcdCtl {
     unsigned flag;
-    uint8_t pad[124];
+    int idle;  // (lane kernel) workgroups of this XCD without any work
+    uint8_t pad[120];
 };
 
 // Counters shared by every wavefront of a launch.  The ones wavefronts
@@ -122,11 +123,12 @@ struct SearchParams {
                                      // search per wavefront)
     int seg_bytes;                   // segmented kernel: LDS bytes per search (seg_layout)
     int arows;                       // segmented kernel: adjacency rows kept per graph in LDS
-    int lane_kc;                     // lane kernel: classes of a top frame kept in LDS
+    int lane_rc;                     // lane kernel: stack entries of a lane in LDS (a ring)
     int lane_stride;                 // lane kernel: bytes of one lane's stack in HBM
     int lane_map_bytes;              // ... of which the mapping takes the first
     int lane_big;                    // lane kernel: entries of a wavefront's worst-case area
-    int pad_lane;
+    int check_ticks;                 // lane kernel: a workgroup looks at what all XCDs share
+                                     // once in so many realtime ticks
 };
 
 struct ResetParams {
@@ -232,6 +234,8 @@ inline constexpr int lane_hdr_entries(int word_bytes) { return word_bytes == 4 ?
 inline constexpr int lane_worst_entries(int word_bytes, int m) {
     return m * (m + 1) / 2 + (m + 1) * lane_hdr_entries(word_bytes);
 }
+// LDS of a workgroup beside its wavefronts' parts (Team, at most).
+constexpr int kLaneTeamBytes = 2048;
 inline constexpr int lane_map_bytes_for(int m) { return align16(2 * (m + 1)); }
 
 inline int slot_bytes_for(int word_bytes, int mmax) {
