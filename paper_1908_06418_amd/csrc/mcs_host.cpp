@@ -7,6 +7,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -59,8 +61,11 @@ bool in_arc(const mcs_graph &g, int i, int j) {
 struct Bits {
     uint64_t w[4] = {0, 0, 0, 0};
     void set(int j) { w[j >> 6] |= 1ull << (j & 63); }
-    bool get(int j) const { return (w[j >> 6] >> (j & 63)) & 1; }
     bool any() const { return (w[0] | w[1] | w[2] | w[3]) != 0; }
+    int size() const {
+        return __builtin_popcountll(w[0]) + __builtin_popcountll(w[1]) +
+               __builtin_popcountll(w[2]) + __builtin_popcountll(w[3]);
+    }
 };
 
 Bits first_n(int n) {
@@ -70,8 +75,37 @@ Bits first_n(int n) {
     return b;
 }
 
-// Checks one graph; returns MCS_OK or an error with a message.
+// Calls f(i, j) for every arc i -> j, row by row: the set bits only, so a
+// sparse graph costs its arcs and not n^2 look-ups.
+template <class F>
+void for_arcs(const mcs_graph &g, F f) {
+    const int rw = row_words(g.n);
+    for (int i = 0; i < g.n; i++)
+        for (int k = 0; k < rw; k++)
+            for (uint64_t x = g.adj[(size_t)i * rw + k]; x; x &= x - 1)
+                f(i, 64 * k + __builtin_ctzll(x));
+}
+
+// Whether the graph has none of the faults that validate() names.
+bool sound(const mcs_graph &g) {
+    if (g.n < 0 || g.n > MCS_MAX_N || (g.n > 0 && !g.adj) || (g.directed != 0 && g.directed != 1))
+        return false;
+    const int rw = row_words(g.n);
+    uint64_t bad = 0;
+    for (int i = 0; i < g.n; i++)
+        for (int k = 0; k < rw; k++)
+            bad |= g.adj[(size_t)i * rw + k] & ~low_mask(g.n - 64 * k);
+    if (bad)
+        return false;
+    for_arcs(g, [&](int i, int j) { bad |= i == j || (!g.directed && !in_arc(g, j, i)); });
+    return !bad;
+}
+
+// Checks one graph; returns MCS_OK or an error with a message (the search
+// for the first fault, by pairs of vertices, only where there is one).
 mcs_status validate(const mcs_graph &g, const char *which, int idx) {
+    if (sound(g))
+        return MCS_OK;
     char buf[160];
     if (g.n < 0) {
         snprintf(buf, sizeof buf, "%s[%d]: negative vertex count", which, idx);
@@ -115,9 +149,11 @@ mcs_status validate(const mcs_graph &g, const char *which, int idx) {
 // Descending degree (out + in when directed), ties by index (Sec. IV.A).
 std::vector<int> degree_order(const mcs_graph &g) {
     std::vector<int> deg(g.n, 0), ord(g.n);
-    for (int i = 0; i < g.n; i++)
-        for (int j = 0; j < g.n; j++)
-            deg[i] += (int)in_arc(g, i, j) + (g.directed ? (int)in_arc(g, j, i) : 0);
+    for_arcs(g, [&](int i, int j) {
+        deg[i]++;
+        if (g.directed)
+            deg[j]++;
+    });
     for (int i = 0; i < g.n; i++)
         ord[i] = i;
     std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return deg[a] > deg[b]; });
@@ -237,10 +273,10 @@ std::vector<int> btf_order(const mcs_graph &g) {
 // rows of the relabelled graph: vertex p is original ord[p]
 std::vector<Bits> permuted_rows(const mcs_graph &g, const std::vector<int> &ord) {
     std::vector<Bits> rows(g.n);
+    int at[MCS_MAX_N];
     for (int p = 0; p < g.n; p++)
-        for (int q = 0; q < g.n; q++)
-            if (in_arc(g, ord[p], ord[q]))
-                rows[p].set(q);
+        at[ord[p]] = p;
+    for_arcs(g, [&](int i, int j) { rows[at[i]].set(at[j]); });
     return rows;
 }
 
@@ -248,9 +284,9 @@ std::vector<Bits> transpose_rows(const std::vector<Bits> &rows) {
     int n = (int)rows.size();
     std::vector<Bits> t(n);
     for (int i = 0; i < n; i++)
-        for (int j = 0; j < n; j++)
-            if (rows[i].get(j))
-                t[j].set(i);
+        for (int k = 0; k < 4; k++)
+            for (uint64_t x = rows[i].w[k]; x; x &= x - 1)
+                t[64 * k + __builtin_ctzll(x)].set(i);
     return t;
 }
 
@@ -321,7 +357,6 @@ struct mcs_plan {
     // results of the last run
     std::vector<int> h_inc, h_open, h_dead;
     std::vector<unsigned long long> h_nodes, h_tbest, h_tproof;
-    std::vector<uint16_t> h_maps;
     std::vector<uint8_t> h_out;  // the result range as copied back
     mcs::DevGlobals h_glob{};
     bool have_results = false;
@@ -342,22 +377,14 @@ struct mcs_plan {
 
 namespace {
 
-template <typename W>
-void put_word(std::vector<uint8_t> &buf, uint64_t x) {
-    W w = (W)x;
-    const uint8_t *p = (const uint8_t *)&w;
-    buf.insert(buf.end(), p, p + sizeof(W));
-}
-
 // One row word as the kernels read it: 32, 64, 128 or 256 bits (low
-// 64-bit word first).
+// 64-bit word first; the host's byte order is the device's).
+void pack_word(uint8_t *at, int word_bytes, const Bits &x) { std::memcpy(at, x.w, word_bytes); }
+
 void pack_word(std::vector<uint8_t> &buf, int word_bytes, const Bits &x) {
-    if (word_bytes == 4) {
-        put_word<uint32_t>(buf, x.w[0]);
-    } else {
-        for (int k = 0; k < word_bytes / 8; k++)
-            put_word<uint64_t>(buf, x.w[k]);
-    }
+    const size_t at = buf.size();
+    buf.resize(at + word_bytes);
+    pack_word(buf.data() + at, word_bytes, x);
 }
 
 int next_pow2(int x) {
@@ -473,6 +500,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     p->ordG.resize(ndev);
     p->ordH.resize(ndev);
     p->m.resize(ndev);
+    p->adj.resize((size_t)ndev * R * NB * p->word_bytes);
     uint32_t cls_off = 0;
     size_t map_off = 0;
     for (int i = 0; i < ndev; i++) {
@@ -483,40 +511,54 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         p->ordH[i] = order == 1 ? btf_order(h) : degree_order(h);
         std::vector<Bits> rg = permuted_rows(g, p->ordG[i]);
         std::vector<Bits> rh = permuted_rows(h, p->ordH[i]);
-        std::vector<std::vector<Bits>> sets = {rg, rh};
+        // (a set's rows above its graph's size stay zero)
+        uint8_t *at = p->adj.data() + (size_t)i * R * NB * p->word_bytes;
+        auto pack_set = [&](const std::vector<Bits> &rows) {
+            for (size_t j = 0; j < rows.size(); j++)
+                pack_word(at + j * p->word_bytes, p->word_bytes, rows[j]);
+            at += (size_t)NB * p->word_bytes;
+        };
+        pack_set(rg);
+        pack_set(rh);
         if (directed) {
-            sets.push_back(transpose_rows(rg));
-            sets.push_back(transpose_rows(rh));
+            pack_set(transpose_rows(rg));
+            pack_set(transpose_rows(rh));
         }
-        for (int s = 0; s < R; s++)
-            for (int j = 0; j < NB; j++)
-                pack_word(p->adj, p->word_bytes, j < (int)sets[s].size() ? sets[s][j] : Bits{});
 
-        // root classes
-        int K0 = 0;
+        // root classes, in the order of their first vertex of G, and Eq. 1
+        // over them: the largest size any goal needs to consider
+        int K0 = 0, rb = 0;
         if (g.n > 0 && h.n > 0) {
             if (!g.label) {
                 pack_word(p->rootcls, p->word_bytes, first_n(g.n));
                 pack_word(p->rootcls, p->word_bytes, first_n(h.n));
                 K0 = 1;
+                rb = std::min(g.n, h.n);
             } else {
                 std::vector<int> seen;
+                std::vector<Bits> L, Rm;
                 for (int a = 0; a < g.n; a++) {
-                    int lab = g.label[p->ordG[i][a]];
-                    if (std::find(seen.begin(), seen.end(), lab) != seen.end())
+                    const int lab = g.label[p->ordG[i][a]];
+                    const size_t c = std::find(seen.begin(), seen.end(), lab) - seen.begin();
+                    if (c == seen.size()) {
+                        seen.push_back(lab);
+                        L.emplace_back();
+                        Rm.emplace_back();
+                    }
+                    L[c].set(a);
+                }
+                for (int b = 0; b < h.n; b++) {
+                    const int lab = h.label[p->ordH[i][b]];
+                    const size_t c = std::find(seen.begin(), seen.end(), lab) - seen.begin();
+                    if (c < seen.size())
+                        Rm[c].set(b);
+                }
+                for (size_t c = 0; c < seen.size(); c++) {
+                    if (!Rm[c].any())
                         continue;
-                    seen.push_back(lab);
-                    Bits L, Rm;
-                    for (int b = 0; b < g.n; b++)
-                        if (g.label[p->ordG[i][b]] == lab)
-                            L.set(b);
-                    for (int b = 0; b < h.n; b++)
-                        if (h.label[p->ordH[i][b]] == lab)
-                            Rm.set(b);
-                    if (!Rm.any())
-                        continue;
-                    pack_word(p->rootcls, p->word_bytes, L);
-                    pack_word(p->rootcls, p->word_bytes, Rm);
+                    pack_word(p->rootcls, p->word_bytes, L[c]);
+                    pack_word(p->rootcls, p->word_bytes, Rm[c]);
+                    rb += std::min(L[c].size(), Rm[c].size());
                     K0++;
                 }
             }
@@ -537,27 +579,6 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         di.dead_on = p->dead_abs > 0 ? 1 : 0;
         p->inst[i] = di;
         p->K0.push_back(K0);
-        // Eq. 1 at the root: the largest size any goal needs to consider
-        int rb = 0;
-        if (g.n > 0 && h.n > 0) {
-            if (!g.label) {
-                rb = std::min(g.n, h.n);
-            } else {
-                std::vector<int> seen;
-                for (int a = 0; a < g.n; a++) {
-                    int lab = g.label[a];
-                    if (std::find(seen.begin(), seen.end(), lab) != seen.end())
-                        continue;
-                    seen.push_back(lab);
-                    int cg = 0, ch = 0;
-                    for (int b = 0; b < g.n; b++)
-                        cg += g.label[b] == lab;
-                    for (int b = 0; b < h.n; b++)
-                        ch += h.label[b] == lab;
-                    rb += std::min(cg, ch);
-                }
-            }
-        }
         p->root_bound.push_back(rb);
         cls_off += (uint32_t)K0;
         map_off += (size_t)mi * (mi + 1) / 2;
@@ -840,6 +861,22 @@ mcs_status mcs_plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H
 
 size_t mcs_plan_workspace_size(const mcs_plan *p) { return p ? p->ws_bytes : 0; }
 
+// The input image (descriptors, rows, root classes) and the result range
+// (incumbents through the globals) are each one contiguous part of the
+// workspace, so each moves with a single copy.
+static size_t in_begin(const mcs_plan *p) { return p->off_inst; }
+static size_t in_end(const mcs_plan *p) { return p->off_cls + p->rootcls.size(); }
+static size_t out_begin(const mcs_plan *p) { return p->off_inc; }
+static size_t out_end(const mcs_plan *p) { return p->off_glob + sizeof(mcs::DevGlobals); }
+
+// The input image, in_end - in_begin bytes, at img.
+static void stage_inputs(const mcs_plan *p, uint8_t *img) {
+    const size_t b = in_begin(p);
+    std::memcpy(img + (p->off_inst - b), p->inst.data(), sizeof(mcs::DevInst) * p->count);
+    std::memcpy(img + (p->off_adj - b), p->adj.data(), p->adj.size());
+    std::memcpy(img + (p->off_cls - b), p->rootcls.data(), p->rootcls.size());
+}
+
 mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *stream) {
     g_err.clear();
     if (!p)
@@ -856,12 +893,13 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     }
     p->ws = (uint8_t *)workspace;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(p->ws + p->off_inst, p->inst.data(), sizeof(mcs::DevInst) * p->count,
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(p->ws + p->off_adj, p->adj.data(), p->adj.size(), hipMemcpyHostToDevice,
-                           s));
-    HIP_TRY(hipMemcpyAsync(p->ws + p->off_cls, p->rootcls.data(), p->rootcls.size(),
-                           hipMemcpyHostToDevice, s));
+    // one copy of the input image instead of one for each of its parts
+    const size_t img_bytes = in_end(p) - in_begin(p);
+    std::unique_ptr<uint8_t[]> img(new (std::nothrow) uint8_t[img_bytes]());
+    if (!img)
+        return fail(MCS_E_INTERNAL, "out of host memory");
+    stage_inputs(p, img.get());
+    HIP_TRY(hipMemcpyAsync(p->ws + in_begin(p), img.get(), img_bytes, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
 
     mcs::SearchParams &sp = p->sp;
@@ -960,23 +998,6 @@ static mcs_status launch_direct(mcs_plan *p, hipStream_t s) {
     return MCS_OK;
 }
 
-// The input image (descriptors, rows, root classes) and the result range
-// (incumbents through the globals) are each one contiguous part of the
-// workspace, so a graph moves each with a single copy.
-static size_t in_begin(const mcs_plan *p) { return p->off_inst; }
-static size_t in_end(const mcs_plan *p) { return p->off_cls + p->rootcls.size(); }
-static size_t out_begin(const mcs_plan *p) { return p->off_inc; }
-static size_t out_end(const mcs_plan *p) { return p->off_glob + sizeof(mcs::DevGlobals); }
-
-static void stage_inputs(mcs_plan *p) {
-    uint8_t *img = p->pin;
-    const size_t b = in_begin(p);
-    std::memset(img, 0, p->pin_in_bytes);
-    std::memcpy(img + (p->off_inst - b), p->inst.data(), sizeof(mcs::DevInst) * p->count);
-    std::memcpy(img + (p->off_adj - b), p->adj.data(), p->adj.size());
-    std::memcpy(img + (p->off_cls - b), p->rootcls.data(), p->rootcls.size());
-}
-
 // HIP graph of one complete solve: input copy, reset kernel, search kernel
 // (bracketed by the timing events), result copy.  No memset nodes: the reset
 // kernel clears the state with plain stores.
@@ -987,7 +1008,8 @@ static mcs_status build_graph(mcs_plan *p) {
         HIP_TRY(hipHostMalloc((void **)&p->pin, p->pin_in_bytes + p->pin_out_bytes,
                               hipHostMallocDefault));
     }
-    stage_inputs(p);
+    std::memset(p->pin, 0, p->pin_in_bytes);
+    stage_inputs(p, p->pin);
     HIP_TRY(hipGraphCreate(&p->graph, 0));
     hipGraphNode_t nin = nullptr, nr = nullptr, ne0 = nullptr, ns = nullptr, ne1 = nullptr,
                    nout = nullptr;
@@ -1108,8 +1130,7 @@ mcs_status mcs_plan_results(mcs_plan *p, mcs_result *res, void *stream) {
     p->h_nodes = u64s(p->off_nodes);
     p->h_tbest = u64s(p->off_tbest);
     p->h_tproof = u64s(p->off_tproof);
-    p->h_maps.assign((const uint16_t *)(o + (p->off_maps - ob)),
-                     (const uint16_t *)(o + (p->off_maps - ob)) + p->map_pairs);
+    const uint16_t *maps = (const uint16_t *)(o + (p->off_maps - ob));
     std::memcpy(&p->h_glob, o + (p->off_glob - ob), sizeof(mcs::DevGlobals));
     if (p->ev0 && hipEventElapsedTime(&p->last_ms, p->ev0, p->ev1) != hipSuccess) {
         (void)hipGetLastError();
@@ -1156,7 +1177,7 @@ mcs_status mcs_plan_results(mcs_plan *p, mcs_result *res, void *stream) {
             r.t_best_s = (double)(((kb & mask48) - (t0 & mask48)) & mask48) / p->tick_hz;
             size_t off = p->inst[i].map_off + (size_t)size * (size - 1) / 2;
             for (int j = 0; j < size; j++) {
-                uint16_t e = p->h_maps[off + j];
+                uint16_t e = maps[off + j];
                 int pg = e & 0xFF, ph = e >> 8;
                 if (r.map_g)
                     r.map_g[j] = p->ordG[i][pg];
@@ -1222,7 +1243,7 @@ static mcs_status apply_bounds(mcs_plan *p, const int32_t *lb, const int32_t *ta
         di.dead_on = dead_on[k];
     }
     if (p->pin)
-        stage_inputs(p);  // a graph replay copies the descriptors in from here
+        stage_inputs(p, p->pin);  // a graph replay copies the descriptors in from here
     HIP_TRY(hipMemcpyAsync(p->ws + p->off_inst, p->inst.data(), sizeof(mcs::DevInst) * p->count,
                            hipMemcpyHostToDevice, as_stream(stream)));
     HIP_TRY(hipStreamSynchronize(as_stream(stream)));
