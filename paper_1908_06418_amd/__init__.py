@@ -84,7 +84,7 @@ class _Marshal:
         self._flat = None  # (words, labels, their extents per graph)
         try:
             self._marshal_flat(pairs)
-        except (TypeError, ValueError, OverflowError):
+        except (TypeError, ValueError, OverflowError, DeprecationWarning):
             self._flat = None
             self.sizes = []
             self._keep = []

@@ -359,6 +359,7 @@ struct mcs_plan {
     std::vector<unsigned long long> h_nodes, h_tbest, h_tproof;
     std::vector<uint8_t> h_out;  // the result range as copied back
     mcs::DevGlobals h_glob{};
+    mcs::SearchStats h_stats{};  // the sum over its copies
     bool have_results = false;
 
     ~mcs_plan() {
@@ -1132,6 +1133,23 @@ mcs_status mcs_plan_results(mcs_plan *p, mcs_result *res, void *stream) {
     p->h_tproof = u64s(p->off_tproof);
     const uint16_t *maps = (const uint16_t *)(o + (p->off_maps - ob));
     std::memcpy(&p->h_glob, o + (p->off_glob - ob), sizeof(mcs::DevGlobals));
+    p->h_stats = p->h_glob.st[0];
+    for (int k = 1; k < mcs::kRings; k++) {
+        const mcs::SearchStats &a = p->h_glob.st[k];
+        mcs::SearchStats &z = p->h_stats;
+        z.t0 = std::min(z.t0, a.t0);
+        z.batches += a.batches;
+        z.children += a.children;
+        z.lane_slots += a.lane_slots;
+        z.donations += a.donations;
+        z.pops += a.pops;
+        z.busy_ticks += a.busy_ticks;
+        z.hbm_frames += a.hbm_frames;
+        z.pushed_classes += a.pushed_classes;
+        z.sleep_ticks += a.sleep_ticks;
+        z.node_classes += a.node_classes;
+        z.max_stack = std::max(z.max_stack, a.max_stack);
+    }
     if (p->ev0 && hipEventElapsedTime(&p->last_ms, p->ev0, p->ev1) != hipSuccess) {
         (void)hipGetLastError();
         p->last_ms = 0.f;
@@ -1144,7 +1162,7 @@ mcs_status mcs_plan_results(mcs_plan *p, mcs_result *res, void *stream) {
                                            : "a search wavefront hit an internal capacity check");
 
     const unsigned long long mask48 = 0xFFFFFFFFFFFFull;
-    const unsigned long long t0 = p->h_glob.t0;
+    const unsigned long long t0 = p->h_stats.t0;
     bool all_proven = true;
     for (int k = 0; k < p->pairs; k++) {
         mcs_result &r = res[k];
@@ -1198,33 +1216,33 @@ mcs_status mcs_plan_stats(const mcs_plan *p, mcs_stats *st) {
     mcs_stats z{};
     for (int i = 0; i < p->count; i++)
         z.nodes += (int64_t)p->h_nodes[i];
-    z.batches = (int64_t)p->h_glob.batches;
-    z.children = (int64_t)p->h_glob.children;
-    z.lane_slots = (int64_t)p->h_glob.lane_slots;
-    z.donations = (int64_t)p->h_glob.donations;
-    z.pops = (int64_t)p->h_glob.pops;
+    z.batches = (int64_t)p->h_stats.batches;
+    z.children = (int64_t)p->h_stats.children;
+    z.lane_slots = (int64_t)p->h_stats.lane_slots;
+    z.donations = (int64_t)p->h_stats.donations;
+    z.pops = (int64_t)p->h_stats.pops;
     z.waves = p->waves;
     z.blocks = p->blocks;
     z.lds_per_wave = p->lds_per_wave;
     z.stopped = p->h_glob.stop ? 1 : 0;
     z.kernel_ms = p->last_ms;
-    z.busy_wave_s = (double)p->h_glob.busy_ticks / p->tick_hz;
-    z.hbm_frames = (int64_t)p->h_glob.hbm_frames;
-    z.sleep_wave_s = (double)p->h_glob.sleep_ticks / p->tick_hz;
+    z.busy_wave_s = (double)p->h_stats.busy_ticks / p->tick_hz;
+    z.hbm_frames = (int64_t)p->h_stats.hbm_frames;
+    z.sleep_wave_s = (double)p->h_stats.sleep_ticks / p->tick_hz;
     // Algorithmic LDS bytes: each child batch reads the rows of v and of
     // its C partners (one word each, two when directed); each pushed frame's
     // classes (L and R words) are written once and read twice (at the descent
     // and when the search returns to the frame).
     {
         // (the segmented kernel reads both rows per child; "batches" are its steps)
-        const int64_t rows = p->seg_log ? 2 * (int64_t)p->h_glob.children
-                                        : (int64_t)p->h_glob.batches + (int64_t)p->h_glob.children;
+        const int64_t rows = p->seg_log ? 2 * (int64_t)p->h_stats.children
+                                        : (int64_t)p->h_stats.batches + (int64_t)p->h_stats.children;
         const int rw = (p->directed ? 2 : 1) * p->word_bytes;
-        z.lds_bytes = rows * rw + (int64_t)p->h_glob.pushed_classes * 3 * 2 * p->word_bytes;
+        z.lds_bytes = rows * rw + (int64_t)p->h_stats.pushed_classes * 3 * 2 * p->word_bytes;
     }
-    z.node_classes = (int64_t)p->h_glob.node_classes;
+    z.node_classes = (int64_t)p->h_stats.node_classes;
     z.stack_classes = p->cap_classes;
-    z.max_stack_used = p->h_glob.max_stack;
+    z.max_stack_used = p->h_stats.max_stack;
     *st = z;
     return MCS_OK;
 }

@@ -107,6 +107,7 @@ using KernArgs = __attribute__((address_space(4))) SearchParams;
 DEV int shfl_any(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
 
 // What the wavefronts of a workgroup share.
+constexpr int kTeamStats = 10;
 struct Team {
     unsigned hungry;      // bit w: wavefront w waits for a frame
     unsigned done;        // the search is over
@@ -120,6 +121,9 @@ struct Team {
     int inc[16];          // the incumbent as last seen or raised
     unsigned seen[16];    // ticks of the last look at it
     u64w nodes[16];       // counted by wavefronts that have left
+    unsigned left;        // wavefronts that have not ended
+    int max_stack;
+    u64w st[kTeamStats];  // the wavefronts' statistics
 };
 static_assert(sizeof(Team) <= kLaneTeamBytes, "the host leaves room for it in LDS");
 template <typename T>
@@ -1512,8 +1516,6 @@ struct LaneSearch {
 
     __device__ void main_loop() {
         t_start = now_ticks();
-        if (lane == 0)
-            a_min64(&P.g->t0, t_start);
         const bool share = !P.single_wave && P.donate_low >= 0;
         const int check_interval = sc(P.check_interval);
         int since_steal = 0, since_feed = 0;
@@ -1565,19 +1567,28 @@ struct LaneSearch {
                                                     __HIP_MEMORY_SCOPE_WORKGROUP));
         }
         const int mu = (int)~wave_min(~(uint32_t)max_used);
+        int last = 0;
         if (lane == 0) {
-            a_add64(&P.g->batches, n_steps);
-            a_add64(&P.g->children, n_child);
-            a_add64(&P.g->lane_slots, n_child);
-            a_add64(&P.g->donations, n_don);
-            a_add64(&P.g->pops, n_pops);
-            a_add64(&P.g->busy_ticks, n_busy);
-            a_add64(&P.g->hbm_frames, n_big);
-            a_add64(&P.g->pushed_classes, n_pushed);
-            a_add64(&P.g->sleep_ticks, n_sleep);
-            a_add64(&P.g->node_classes, n_ncls);
-            __hip_atomic_fetch_max(&P.g->max_stack, mu, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            const u64w x[kTeamStats] = {n_steps, n_child, n_child, n_don, n_pops,
+                                        n_busy, n_big, n_pushed, n_sleep, n_ncls};
+            for (int i = 0; i < kTeamStats; ++i)
+                __hip_atomic_fetch_add(&T.st[i], x[i], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_max(&T.max_stack, mu, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            last = (int)__hip_atomic_fetch_add(&T.left, ~0u, __ATOMIC_ACQ_REL,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        if (rl(last, 0) == 1) {
+            // the workgroup's last wavefront hands in its sums
+            static_assert(offsetof(SearchStats, node_classes) == 8 * kTeamStats, "in this order");
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            SearchStats *g = &P.g->st[my_ring];
+            if (lane < kTeamStats)
+                a_add64(&g->batches + lane, T.st[lane]);
+            else if (lane == kTeamStats)
+                __hip_atomic_fetch_max(&g->max_stack, T.max_stack, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 };
@@ -1590,11 +1601,17 @@ __global__ void __launch_bounds__(sizeof(W) <= 8 ? 1024 : 512) mcs_lane_kernel(S
     __shared__ Team T;
     const KernArgs &P = *(const KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     if (threadIdx.x == 0) {
+        // (before the barrier: no wavefront of the workgroup starts earlier)
+        a_min64(&P.g->st[blockIdx.x & (kRings - 1)].t0, now_ticks());
         T.hungry = 0;
         T.done = 0;
         T.looked = 0;
         T.idle = 0;
+        T.left = Pk.single_wave ? 1u : blockDim.x >> 6;
+        T.max_stack = 0;
     }
+    if (threadIdx.x < kTeamStats)
+        T.st[threadIdx.x] = 0;
     if (threadIdx.x < 16) {
         T.full[threadIdx.x] = 0;
         T.ref[threadIdx.x] = 0;

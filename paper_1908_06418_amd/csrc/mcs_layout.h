@@ -44,6 +44,29 @@ struct XcdCtl {
     uint8_t pad[120];
 };
 
+// What a launch's wavefronts count, one copy per XCD (the host adds them up):
+// every one adds its own at its end, and a line takes one atomic of the device
+// every few nanoseconds.  With one copy a launch of 1,024 wavefronts took
+// 80 us for these alone.
+struct SearchStats {
+    unsigned long long t0;          // earliest wavefront start (realtime ticks)
+    unsigned long long batches;
+    unsigned long long children;
+    unsigned long long lane_slots;
+    unsigned long long donations;
+    unsigned long long pops;
+    unsigned long long busy_ticks;  // realtime ticks wavefronts spent searching
+    unsigned long long hbm_frames;  // frames placed in the HBM part of a class stack
+    unsigned long long pushed_classes;  // classes in the frames pushed onto LDS stacks
+    unsigned long long sleep_ticks; // realtime ticks idle wavefronts spent sleeping
+    unsigned long long node_classes;    // classes split, summed over the matched
+                                        // children counted as nodes (first
+                                        // evaluations only)
+    int max_stack;                  // most classes any wavefront's stack held
+    uint8_t pad[36];
+};
+static_assert(sizeof(SearchStats) == 128, "one line");
+
 // Counters shared by every wavefront of a launch.  The ones wavefronts
 // update each sit on a cache line of their own.
 struct DevGlobals {
@@ -55,25 +78,12 @@ struct DevGlobals {
     uint8_t pad_state[120];
     unsigned next_inst;             // next instance whose root is not yet taken
     uint8_t pad_next[124];
-    unsigned long long t0;          // earliest wavefront start (realtime ticks)
     unsigned long long node_total;  // nodes flushed so far (for the node limit)
     unsigned error;                 // nonzero: a capacity check fired
-    int pad0;
-    unsigned long long batches;     // statistics
-    unsigned long long children;
-    unsigned long long lane_slots;
-    unsigned long long donations;
-    unsigned long long pops;
-    unsigned long long busy_ticks;  // realtime ticks wavefronts spent searching
-    unsigned long long hbm_frames;  // frames placed in the HBM part of a class stack
-    unsigned long long sleep_ticks; // realtime ticks idle wavefronts spent sleeping
-    unsigned long long pushed_classes;  // classes in the frames pushed onto LDS stacks
-    unsigned long long node_classes;    // classes split, summed over the matched
-                                        // children counted as nodes (first
-                                        // evaluations only)
-    int max_stack;                  // most classes any wavefront's stack held
-    int pad1;
+    uint8_t pad_total[116];
+    SearchStats st[kRings];
 };
+static_assert(sizeof(DevGlobals) % 8 == 0, "the reset kernel writes it in words");
 
 struct SearchParams {
     const DevInst *inst;

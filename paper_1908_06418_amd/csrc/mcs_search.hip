@@ -1451,7 +1451,7 @@ struct Searcher {
     __device__ void main_loop() {
         t_start = now_ticks();
         if (lane == 0)
-            a_min64(&P.g->t0, t_start);
+            a_min64(&P.g->st[my_ring].t0, t_start);
         int backoff = 0;
         for (;;) {
             bool got = false;
@@ -1491,16 +1491,16 @@ struct Searcher {
         }
         fold();
         if (lane == 0) {
-            a_add64(&P.g->batches, n_batches);
-            a_add64(&P.g->children, n_children);
-            a_add64(&P.g->lane_slots, n_lanes);
-            a_add64(&P.g->donations, n_don);
-            a_add64(&P.g->pops, n_pops);
-            a_add64(&P.g->busy_ticks, n_busy);
-            a_add64(&P.g->pushed_classes, n_pushed);
-            a_add64(&P.g->node_classes, n_ncls);
-            a_add64(&P.g->sleep_ticks, n_sleep);
-            __hip_atomic_fetch_max(&P.g->max_stack, max_used, __ATOMIC_RELAXED,
+            a_add64(&P.g->st[my_ring].batches, n_batches);
+            a_add64(&P.g->st[my_ring].children, n_children);
+            a_add64(&P.g->st[my_ring].lane_slots, n_lanes);
+            a_add64(&P.g->st[my_ring].donations, n_don);
+            a_add64(&P.g->st[my_ring].pops, n_pops);
+            a_add64(&P.g->st[my_ring].busy_ticks, n_busy);
+            a_add64(&P.g->st[my_ring].pushed_classes, n_pushed);
+            a_add64(&P.g->st[my_ring].node_classes, n_ncls);
+            a_add64(&P.g->st[my_ring].sleep_ticks, n_sleep);
+            __hip_atomic_fetch_max(&P.g->st[my_ring].max_stack, max_used, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -1540,15 +1540,26 @@ __global__ void __launch_bounds__(256) mcs_reset_kernel(ResetParams R) {
     }
     for (int i = tid; i < kRings * R.ring_slots; i += stride)
         R.seq[i] = (unsigned long long)(i % R.ring_slots);
-    if (tid == 0) {
-        DevGlobals z = {};
-        z.t0 = ~0ull;
-        z.open_total = R.count;
-        if (R.count == 0)
-            for (int k = 0; k < kRings; ++k)
-                z.xcd[k].flag = kFlagDone;
-        *R.g = z;
+    // The globals are zero but for a few words, each written by one thread (a
+    // single thread storing all of them took 40 us of every launch).
+    unsigned long long *g = (unsigned long long *)R.g;
+    for (int i = tid; i < (int)(sizeof(DevGlobals) / 8); i += stride) {
+        const int at = 8 * i;
+        unsigned long long x = 0;
+        if (at == offsetof(DevGlobals, open_total))
+            x = (unsigned)R.count;  // (with stop, 0, in the same word)
+        const int s = at - (int)offsetof(DevGlobals, st);
+        if (s >= 0 && s % (int)sizeof(SearchStats) == 0)
+            x = ~0ull;  // t0
+        const int c = at - (int)offsetof(DevGlobals, xcd);
+        if (R.count == 0 && c >= 0 && c < (int)sizeof(XcdCtl) * kRings &&
+            c % (int)sizeof(XcdCtl) == 0)
+            x = kFlagDone;  // (with idle, 0)
+        g[i] = x;
     }
+    static_assert(offsetof(DevGlobals, open_total) % 8 == 0 &&
+                  offsetof(DevGlobals, stop) == offsetof(DevGlobals, open_total) + 4 &&
+                  offsetof(SearchStats, t0) == 0 && offsetof(XcdCtl, flag) == 0, "as written here");
 }
 
 }  // namespace mcs

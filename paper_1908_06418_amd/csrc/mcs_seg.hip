@@ -1167,7 +1167,7 @@ struct SegSearch {
     __device__ void main_loop() {
         t_start = now_ticks();
         if (lane == 0)
-            a_min64(&P.g->t0, t_start);
+            a_min64(&P.g->st[my_ring].t0, t_start);
         int backoff = 0;
         int idle_steps = 0;
         int refill_gap = 16;  // steps between refills while some segments are busy
@@ -1230,20 +1230,20 @@ struct SegSearch {
         n_hbm = seg_total(n_hbm);
         n_ncls = seg_total(n_ncls);
         if (lane == 0) {
-            a_add64(&P.g->batches, n_steps);
-            a_add64(&P.g->children, n_evals);
-            a_add64(&P.g->lane_slots, n_lanes);
-            a_add64(&P.g->donations, n_don);
-            a_add64(&P.g->pops, n_pops);
-            a_add64(&P.g->busy_ticks, n_busy);
-            a_add64(&P.g->hbm_frames, n_hbm);
-            a_add64(&P.g->pushed_classes, n_pushed);
-            a_add64(&P.g->sleep_ticks, n_sleep);
-            a_add64(&P.g->node_classes, n_lanes + n_ncls);
+            a_add64(&P.g->st[my_ring].batches, n_steps);
+            a_add64(&P.g->st[my_ring].children, n_evals);
+            a_add64(&P.g->st[my_ring].lane_slots, n_lanes);
+            a_add64(&P.g->st[my_ring].donations, n_don);
+            a_add64(&P.g->st[my_ring].pops, n_pops);
+            a_add64(&P.g->st[my_ring].busy_ticks, n_busy);
+            a_add64(&P.g->st[my_ring].hbm_frames, n_hbm);
+            a_add64(&P.g->st[my_ring].pushed_classes, n_pushed);
+            a_add64(&P.g->st[my_ring].sleep_ticks, n_sleep);
+            a_add64(&P.g->st[my_ring].node_classes, n_lanes + n_ncls);
         }
         const int mu = wave_max_i(max_used);
         if (lane == 0)
-            __hip_atomic_fetch_max(&P.g->max_stack, mu, __ATOMIC_RELAXED,
+            __hip_atomic_fetch_max(&P.g->st[my_ring].max_stack, mu, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
     }
 
