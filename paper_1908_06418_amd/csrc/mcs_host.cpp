@@ -333,7 +333,7 @@ struct mcs_plan {
     int seg_log = 0;   // 3 or 4: searches of 2^seg_log lanes (mcs_seg.hip); 0: one per wavefront
     int seg_bytes = 0, arows = 0;
     bool lane = false;  // a search in every lane (mcs_lane.hip)
-    int lane_rc = 0, lane_stride = 0, lane_big = 0;
+    int lane_rc = 0, lane_stride = 0, lane_map = 0, lane_big = 0;
     double tick_hz = 1e8;
 
     uint8_t *ws = nullptr;
@@ -416,6 +416,13 @@ const char *mcs_last_error(void) { return g_err.c_str(); }
 
 // may_lane: the kernel with a search in every lane may be chosen (the
 // static-scratch entry keeps the kernels whose stacks fit there).
+static void *search_fn(const mcs_plan *p) {
+    if (p->lane)
+        return mcs_internal_seg_kernel(p->word_bytes, p->directed, p->policy ? -1 : 0);
+    return p->seg_log ? mcs_internal_seg_kernel(p->word_bytes, p->directed, p->seg_log)
+                      : mcs_internal_search_kernel(p->word_bytes, p->directed, p->policy != nullptr);
+}
+
 static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H,
                               const mcs_opts *opts, mcs_plan **out, bool may_lane) {
     g_err.clear();
@@ -611,10 +618,9 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     (void)hipGetLastError();
     p->tick_hz = (double)clock_khz * 1000.0;
     const bool wide = p->word_bytes >= 16;
-    // Search layout: one search per lane segment of 16 (or 8) lanes
-    // (mcs_seg.hip), or one per wavefront (mcs_search.hip: needed for
-    // 128-bit rows and for the learned policy, which scores one vertex per
-    // lane).
+    // Search layout: one search per lane (mcs_lane.hip), one per segment of
+    // 4, 8 or 16 lanes (mcs_seg.hip, rows of up to 64 bits), or one per
+    // wavefront (mcs_search.hip).
     {
         const int sl = p->tun.seg_lanes;
         if (sl != 0 && sl != 4 && sl != 8 && sl != 16 && sl != 64) {
@@ -624,7 +630,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         if (wide || p->policy || sl == 64)
             p->seg_log = 0;
         else
-            p->seg_log = sl == 4 ? 2 : sl == 16 ? 4 : 3;  // default: 8 lanes
+            p->seg_log = sl == 4 ? 2 : sl == 16 ? 4 : 3;  // unless seg_lanes says: 8 lanes
         // The default is a search in every lane (mcs_lane.hip), unless a knob
         // of another kernel is set.  With wide rows only if no instance can
         // dive deep: a frame of close to n classes is one long loop of a
@@ -638,8 +644,13 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         bool deep = false;
         for (int i = 0; wide && i < ndev; i++)
             deep = deep || 8 * p->root_bound[i] > 7 * p->m[i];
-        p->lane = may_lane && sl == 0 && !p->policy && p->tun.stack_classes <= 0 && !deep &&
-                  !(wide && p->tun.children_per_wave > 0);
+        // One search alone is a single lane there, 1.1 us a node against 0.65
+        // on a segment and less on a wavefront.  The learned policy goes with
+        // it: 24 pairs of 28 vertices take 152 ms with a search per wavefront
+        // and 34 with one per lane.
+        p->lane = may_lane && sl == 0 && p->tun.stack_classes <= 0 && !deep &&
+                  !p->tun.single_wave &&
+                  !((wide || p->policy) && p->tun.children_per_wave > 0);
         if (p->lane)
             p->seg_log = 0;
     }
@@ -771,9 +782,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     }
     p->waves_per_block = wpb;
     p->lds_per_block = wpb * p->lds_per_wave;
-    const void *kern = p->seg_log || p->lane ? mcs_internal_seg_kernel(p->word_bytes, directed, p->seg_log)
-                                  : mcs_internal_search_kernel(p->word_bytes, directed,
-                                                               p->policy != nullptr);
+    const void *kern = search_fn(p);
     int per_cu = 0;
     if (p->lds_per_block > 65536)
         (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -810,7 +819,10 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     // classes)
     size_t hstacks = 0;
     if (p->lane) {
-        p->lane_stride = (int)((mcs::lane_map_bytes_for(p->mmax) + p->cap_classes * entry + 127) / 128 * 128);
+        // a lane's part: its mapping, with the learned policy the orders of its
+        // shallow frames' partners (64 bytes each), its entries
+        p->lane_map = mcs::lane_map_bytes_for(p->mmax) + 64 * p->policy_levels;
+        p->lane_stride = (p->lane_map + p->cap_classes * entry + 127) / 128 * 128;
         p->lane_big = worst_e;
         p->hstack_stride = align256((size_t)64 * p->lane_stride + (size_t)worst_e * entry);
         hstacks = (size_t)p->waves;
@@ -956,7 +968,7 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.arows = p->arows;
     sp.lane_rc = p->lane_rc;
     sp.lane_stride = p->lane_stride;
-    sp.lane_map_bytes = mcs::lane_map_bytes_for(p->mmax);
+    sp.lane_map_bytes = p->lane_map;
     sp.lane_big = p->lane_big;
     sp.check_ticks = p->tun.check_interval > 0 ? 0 : (int)(p->tick_hz * 10e-6);
 
@@ -975,11 +987,6 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     rp.ring_slots = p->ring_slots;
     p->uploaded = true;
     return MCS_OK;
-}
-
-static void *search_fn(const mcs_plan *p) {
-    return p->seg_log || p->lane ? mcs_internal_seg_kernel(p->word_bytes, p->directed, p->seg_log)
-                      : mcs_internal_search_kernel(p->word_bytes, p->directed, p->policy != nullptr);
 }
 
 static mcs_status launch_direct(mcs_plan *p, hipStream_t s) {

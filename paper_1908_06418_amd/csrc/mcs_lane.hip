@@ -52,6 +52,7 @@
 // carry most of the frames.  A work unit, for the termination counts, is one instance on one
 // wavefront, however many of its lanes work on it.
 #include "mcs_device.h"
+#include "mcs_policy.h"
 
 namespace mcs {
 
@@ -84,6 +85,8 @@ constexpr int kSel = 8;        // class and v are to be chosen
 constexpr int kPatch = 16;     // (with kSel) v is to be taken out of the selected class first
 constexpr int kRow = 32;       // v's G rows are to be loaded
 constexpr int kBig = 8;        // (saved headers) the child frame starts the worst-case area
+constexpr int kPolV = 64;      // the policy has yet to choose v,
+constexpr int kPolW = 128;     // to put the partners in order
 constexpr int kSaved = kUnm | kLe | kOne;
 
 constexpr unsigned kErrMapping = 2;  // codes of DevGlobals::error
@@ -135,7 +138,7 @@ DEV void st_wg(T *p, T v) {
 
 }  // namespace
 
-template <typename W, bool DIR>
+template <typename W, bool DIR, bool POL>
 struct LaneSearch {
     static constexpr int NB = bits_of<W>();
     static constexpr int NR = DIR ? 4 : 2;                  // row sets, and parts of a class
@@ -144,6 +147,8 @@ struct LaneSearch {
     static constexpr int HE = lane_hdr_entries((int)sizeof(W));  // entries of a frame header
     static constexpr int NP = EB >= 16 ? EB / 16 : 1;       // 16-byte pieces of an entry
     static constexpr bool LROWS = sizeof(W) <= 8;           // rows in LDS
+
+    static_assert(!(POL && sizeof(W) > 8), "the policy takes rows of at most 64 bits");
 
     struct Ent {
         u64w w[EW];
@@ -224,18 +229,18 @@ struct LaneSearch {
 
     // Byte offset of entry e of lane l's stack in HBM: its own part below
     // cap, the wavefront's worst-case area from cap on.
-    __device__ uint32_t at(int l, int e) const {
+    __device__ __forceinline__ uint32_t at(int l, int e) const {
         return e < cap ? (uint32_t)l * stride + map_bytes + (uint32_t)e * EB
                        : big_off + (uint32_t)(e - cap) * EB;
     }
     // Slot of entry e (e < 2^16 and rc < 2^8: the rounded quotient is exact).
-    __device__ int slot_of(int e) const {
+    __device__ __forceinline__ int slot_of(int e) const {
         return e - rc * (int)(((float)e + 0.5f) * rinv);
     }
-    __device__ int wrap(int s) const {  // s < 2 rc
+    __device__ __forceinline__ int wrap(int s) const {  // s < 2 rc
         return (int)umin((uint32_t)s, (uint32_t)(s - rc));
     }
-    __device__ Ent hget(uint32_t off) const {
+    __device__ __forceinline__ Ent hget(uint32_t off) const {
         Ent x;
         if constexpr (EW == 1) {
             x.w[0] = *(glb_ptr<u64w>)(wst + off);
@@ -249,7 +254,7 @@ struct LaneSearch {
         }
         return x;
     }
-    __device__ void hput(uint32_t off, const Ent &x) const {
+    __device__ __forceinline__ void hput(uint32_t off, const Ent &x) const {
         if constexpr (EW == 1) {
             *(glb_ptr<u64w>)(wst + off) = x.w[0];
         } else {
@@ -260,7 +265,7 @@ struct LaneSearch {
             }
         }
     }
-    __device__ Ent lget(int l, int slot) const {
+    __device__ __forceinline__ Ent lget(int l, int slot) const {
         const int i = slot * 64 + l;
         Ent x;
         if constexpr (EW == 1) {
@@ -275,7 +280,7 @@ struct LaneSearch {
         }
         return x;
     }
-    __device__ void lput(int l, int slot, const Ent &x) const {
+    __device__ __forceinline__ void lput(int l, int slot, const Ent &x) const {
         const int i = slot * 64 + l;
         if constexpr (EW == 1) {
             ((lds_ptr<u64w>)lbuf)[i] = x.w[0];
@@ -288,10 +293,10 @@ struct LaneSearch {
         }
     }
     // Entry e of lane l's stack, whose ring starts at wl.
-    __device__ Ent eget(int l, int e, int wl) const {
+    __device__ __forceinline__ Ent eget(int l, int e, int wl) const {
         return e >= wl ? lget(l, slot_of(e)) : hget(at(l, e));
     }
-    __device__ void eput(int l, int e, int wl, const Ent &x) const {
+    __device__ __forceinline__ void eput(int l, int e, int wl, const Ent &x) const {
         if (e >= wl)
             lput(l, slot_of(e), x);
         else
@@ -325,7 +330,7 @@ struct LaneSearch {
         }
         return c;
     }
-    __device__ Hdr get_hdr(int l, int e, int wl) const {
+    __device__ __forceinline__ Hdr get_hdr(int l, int e, int wl) const {
         Hdr h;
         const Ent a = eget(l, e, wl);
         h.x = (uint32_t)a.w[0];
@@ -341,7 +346,7 @@ struct LaneSearch {
         }
         return h;
     }
-    __device__ void put_hdr(int l, int e, int wl, const Hdr &h) const {
+    __device__ __forceinline__ void put_hdr(int l, int e, int wl, const Hdr &h) const {
         Ent a = {};
         a.w[0] = (u64w)h.x | ((u64w)h.y << 32);
         if constexpr (EW == 1) {
@@ -356,18 +361,18 @@ struct LaneSearch {
             eput(l, e, wl, a);
         }
     }
-    __device__ glb_ptr<uint16_t> map_at(int l) const {
+    __device__ __forceinline__ glb_ptr<uint16_t> map_at(int l) const {
         return (glb_ptr<uint16_t>)(wst + (uint32_t)l * stride);
     }
     // Class k of the lane's top frame.
-    __device__ Cls<W> cget(int k) const { return unpack(eget(lane, base + HE + k, wlo)); }
-    __device__ void cput(int k, const Cls<W> &c) const { eput(lane, base + HE + k, wlo, pack(c)); }
+    __device__ __forceinline__ Cls<W> cget(int k) const { return unpack(eget(lane, base + HE + k, wlo)); }
+    __device__ __forceinline__ void cput(int k, const Cls<W> &c) const { eput(lane, base + HE + k, wlo, pack(c)); }
 
     // f(class k) for each class of the top frames of the lanes that call
     // this, in step.  far: some lane's frame is not all in its ring, or may
     // lose entries to the calls.
     template <typename F>
-    __device__ void each_class(bool far, F f) const {
+    __device__ __forceinline__ void each_class(bool far, F f) const {
         if (!far) {
             // (U reads in flight at a time)
             constexpr int U = EW <= 2 ? kReads : 2;
@@ -392,13 +397,13 @@ struct LaneSearch {
     }
 
     // The ring's lowest entry goes to HBM.
-    __device__ void evict() {
+    __device__ __forceinline__ void evict() {
         hput(at(lane, wlo), lget(lane, wslot));
         wlo += 1;
         wslot = wrap(wslot + 1);
     }
 
-    __device__ W row(int set, int i) const {
+    __device__ __forceinline__ W row(int set, int i) const {
         if constexpr (LROWS)
             return lrow[set * arows + i];
         else
@@ -407,13 +412,13 @@ struct LaneSearch {
 
     // ---- incumbent ----
 
-    __device__ int cap_inc(int x) const { return (target > 0 && x >= target) ? 255 : x; }
-    __device__ void set_inc(int x) {
+    __device__ __forceinline__ int cap_inc(int x) const { return (target > 0 && x >= target) ? 255 : x; }
+    __device__ __forceinline__ void set_inc(int x) {
         x = cap_inc(x);
         inc = x > inc ? x : inc;
     }
     // The incumbent, or 255 where the instance needs no more search.
-    __device__ int read_inc() const {
+    __device__ __forceinline__ int read_inc() const {
         int g = 0;
         if (lane == 0) {
             g = ld_rlx(&P.inc[inc_slot]);
@@ -428,7 +433,7 @@ struct LaneSearch {
     // Lane l's map (size vertex pairs) is a common induced subgraph: raise
     // the instance's incumbent; the wavefront that raised it to `size` writes
     // that size's mapping slot.
-    __device__ void improve(int l, int size) {
+    __device__ __forceinline__ void improve(int l, int size) {
         const DevInst di = P.inst[inst];
         if (size > sc(di.nG < di.nH ? (int)di.nG : (int)di.nH)) {
             fail(kErrMapping);  // only from a broken class partition
@@ -458,7 +463,7 @@ struct LaneSearch {
 
     // ---- the phases of a step ----
 
-    __device__ void pop() {
+    __device__ __forceinline__ void pop() {
         rrem = (W)0;
         flags = 0;
         t -= 1;
@@ -487,7 +492,7 @@ struct LaneSearch {
 
     // The "v unmatched" child takes its parent's place: only the selected
     // class loses v.
-    __device__ void unmatched() {
+    __device__ __forceinline__ void unmatched() {
         const int ub = bound - ((flags & kLe) ? 1 : 0);
         c_unm += 1;
         if (ub <= inc || ((flags & kOne) && K == 1)) {
@@ -499,7 +504,7 @@ struct LaneSearch {
     }
 
     // The top frame (its upper rc entries) back into the ring.
-    __device__ void fetch() {
+    __device__ __forceinline__ void fetch() {
         const int end = base + HE + K;
         const int lo = end - rc > base ? end - rc : base;
         const int hi = wlo < end ? wlo : end;
@@ -521,7 +526,7 @@ struct LaneSearch {
         }
     }
 
-    __device__ void select() {
+    __device__ __forceinline__ void select() {
         if (flags & kPatch) {
             if (flags & kOne) {
                 // the class empties on the G side: the last one takes its place
@@ -547,11 +552,179 @@ struct LaneSearch {
         const int nl = popc(c.L), nr = popc(c.R);
         rrem = c.R;
         flags = kUnm | kRow | (nl <= nr ? kLe : 0) | (nl == 1 ? kOne : 0);
+        if (POL && d <= P.policy_depth)
+            flags |= ((P.policy_mode & 1) ? kPolV : 0) | ((P.policy_mode & 2) ? kPolW : 0);
+    }
+
+    // ---- learned branching policy ----
+
+    // A lane's partner orders, 64 bytes for each |M| up to the policy's depth,
+    // lie between its mapping and its stack.
+    __device__ __forceinline__ uint32_t order_at(int l, int fd) const {
+        return (uint32_t)l * stride + map_bytes - 64u * (uint32_t)(P.policy_levels - fd);
+    }
+
+    // The policy's choices for the top frame of lane l, made by the whole
+    // wavefront: v of the selected class, and the order of its partners.
+    // (The network is evaluated for one vertex at a time, a hidden unit per
+    // lane: some 10,000 instructions a frame, but only the shallow ones come
+    // here, and all of their subtrees' frames take the lanes' own path: 24
+    // pairs of 28 vertices take 34 ms, and 152 with a search per wavefront.)
+    __device__ __forceinline__ void consult(int l) {
+        wave_sync();  // (entries and orders written by other lanes)
+        const int fK = rl(K, l), fd = rl(d, l), fsel = rl(sel, l), fb = rl(base, l);
+        const int fl = rl(flags, l), fw = rl(wlo, l);
+        Cls<W> c;
+        c.L = c.R = (W)0;
+        if (lane < fK)
+            c = unpack(eget(l, fb + HE + lane, fw));
+        const W sl = rl(c.L, fsel), sr = rl(c.R, fsel);
+        const DevInst di = P.inst[inst];
+        const int nl = popc(sl), nr = popc(sr);
+#pragma unroll 1
+        for (int side = 0; side < 2; ++side) {  // (one copy of the scorer)
+            if (!(fl & (side ? kPolW : kPolV)))
+                continue;
+            const W cand = side ? sr : sl;
+            const uint32_t key = score_key(
+                policy_score(side, cand, c, fK, fd, nl, nr, sc((int)(side ? di.nH : di.nG))), cand);
+            if (side == 0) {
+                const uint32_t best = ~wave_min(~key);
+                const int x = ctz((uint64_t)ballot(key == best));
+                if (lane == l)
+                    v = x;
+            } else {
+                int rank = 0;
+                for (W rest = cand; rest; rest &= rest - 1) {
+                    const int u = ctz(rest);
+                    const uint32_t ku = rl(key, u);
+                    rank += ku > key || (ku == key && u < lane) ? 1 : 0;
+                }
+                if (key != 0)
+                    *(glb_ptr<uint8_t>)(wst + order_at(l, fd) + (uint32_t)rank) = (uint8_t)lane;
+            }
+        }
+        if (lane == l)
+            flags &= ~(kPolV | kPolW);
+        wave_sync();
+    }
+    // (lane u) vertex u's score as an ordered integer, 0 if it is no candidate
+    __device__ __forceinline__ uint32_t score_key(float score, const W &cand) const {
+        const uint32_t b = __float_as_uint(score);
+        const bool is_cand = lane < NB && ((cand >> (lane & (NB - 1))) & 1);
+        return is_cand ? ((b & 0x80000000u) ? ~b : (b | 0x80000000u)) : 0u;
+    }
+    // Lane u returns the score of vertex u of cand, a class side of a frame
+    // with fK classes (lane k holds class k) and fd matches: the features
+    // of oracle/policy.py, the network in single precision from the
+    // half-precision parameters.
+    __device__ __forceinline__ float policy_score(int side, const W &cand, const Cls<W> &c, int fK, int fd, int nl,
+                                  int nr, int n) {
+        const float inv = 1.f / (float)(n > 0 ? n : 1);
+        // this lane's class: its set on this side, and its size bucket
+        W mine = (W)0;
+        int bsh = 0;
+        if (lane < fK) {
+            const int x = popc(c.L), y = popc(c.R), m = x < y ? x : y;
+            const int bq = m <= 1 ? 0 : m == 2 ? 1 : m <= 4 ? 2 : m <= 8 ? 3 : m <= 16 ? 4 : 5;
+            mine = side ? c.R : c.L;
+            bsh = 8 * bq;
+        }
+        const int ul = lane & (NB - 1);
+        const bool is_cand = lane < NB && ((cand >> ul) & 1);
+        int mydeg = 0;
+        if (is_cand)
+            mydeg = popc(both_rows(side, ul));
+        const int dmax = (int)~wave_min(~(uint32_t)mydeg);
+        const uint16_t *w = P.policy;
+        float w1[kPolicyF];
+#pragma unroll
+        for (int f = 0; f < kPolicyF; ++f)
+            w1[f] = hf(w[kOffW1 + lane * kPolicyF + f]);
+        const float b1 = hf(w[kOffB1 + lane]), b2 = hf(w[kOffB2 + lane]);
+        const float w3 = hf(w[kOffW3 + lane]), b3 = hf(w[kOffB3]);
+        const uint4 *w2 = (const uint4 *)(w + kOffW2 + lane * kPolicyH);  // 16-byte aligned
+        float out = 0.f;
+        for (W rest = cand; rest; rest &= rest - 1) {
+            const int u = sc((int)ctz(rest));
+            const W row = sc(both_rows(side, u));
+            const int deg = popc(row);
+            // neighbours of u per class, summed per size bucket (each sum is
+            // at most deg < 64, so 8-bit fields cannot carry)
+            const u64w packed = (u64w)popc(row & mine) << bsh;
+            const int lo = wave_sum((int)(uint32_t)packed);
+            const int hi = wave_sum((int)(uint32_t)(packed >> 32));
+            float x[kPolicyF];
+            x[0] = deg * inv;
+            x[1] = nl * inv;
+            x[2] = nr * inv;
+            x[3] = fd * inv;
+            x[4] = fK * inv;
+            int tot = 0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const int cq = q < 4 ? (lo >> (8 * q)) & 0xFF : (hi >> (8 * (q - 4))) & 0xFF;
+                x[6 + q] = cq * inv;
+                tot += cq;
+            }
+            x[5] = tot * inv;
+            x[12] = (float)side;
+            x[13] = deg == dmax ? 1.f : 0.f;
+            x[14] = 0.f;
+            x[15] = 1.f;
+            float h1 = b1;
+#pragma unroll
+            for (int f = 0; f < kPolicyF; ++f)
+                h1 += w1[f] * x[f];
+            h1 = h1 > 0.f ? h1 : 0.f;
+            float a2 = b2;
+#pragma unroll 1
+            for (int i = 0; i < kPolicyH / 8; ++i) {
+                const uint4 q = w2[i];
+                const uint32_t pk[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    a2 += hf((uint16_t)(pk[e] & 0xFFFFu)) * rlf(h1, 8 * i + 2 * e);
+                    a2 += hf((uint16_t)(pk[e] >> 16)) * rlf(h1, 8 * i + 2 * e + 1);
+                }
+            }
+            const float z = b3 + fwave_sum(w3 * (a2 > 0.f ? a2 : 0.f));
+            out = lane == u ? z : out;
+        }
+        return out;
+    }
+    __device__ __forceinline__ W both_rows(int side, int u) const {
+        W r = row(side, u);
+        if constexpr (DIR)
+            r = r | row(2 + side, u);
+        return r;
+    }
+    // Whether the lane's top frame has its partners in the policy's order.
+    __device__ __forceinline__ bool ordered() const {
+        return POL && d <= P.policy_depth && (P.policy_mode & 2);
+    }
+    // The first two partners left in that order (w1 = w0 if there is one).
+    __device__ __forceinline__ void next_ordered(int &w0, int &w1) const {
+        const int want = popc(rrem) > 1 ? 2 : 1;
+        const uint32_t o = order_at(lane, d);
+        int found = 0;
+        for (int q = 0; q < 8 && ballot(found < want) != 0; ++q) {
+            const u64w x = *(glb_ptr<u64w>)(wst + o + 8u * (uint32_t)q);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int u = (int)(x >> (8 * j)) & 0xFF;
+                if (found < want && u < NB && ((rrem >> (u & (NB - 1))) & 1)) {
+                    w0 = found == 0 ? u : w0;
+                    w1 = u;
+                    found += 1;
+                }
+            }
+        }
     }
 
     // Parts of class c for the child (v, w) by adjacency letter; v and w are
     // still in the part without edges.
-    __device__ void split(const Cls<W> &c, const W &ho, const W &hi, W *pl, W *pr) const {
+    __device__ __forceinline__ void split(const Cls<W> &c, const W &ho, const W &hi, W *pl, W *pr) const {
         if constexpr (!DIR) {
             pl[1] = c.L & go;
             pr[1] = c.R & ho;
@@ -575,11 +748,17 @@ struct LaneSearch {
     // Eq. 1 bounds, from one pass over the classes and one count of v's side.
     // The first that survives is (w, b); a second one that is pruned is done
     // too, one that would survive waits until the search is back.
-    __device__ bool evaluate(int &w, int &b) {
-        const int w0 = ctz(rrem);
-        const W r1 = rrem & (rrem - (W)1);
+    __device__ __forceinline__ bool evaluate(int &w, int &b) {
+        int w0 = ctz(rrem);
+        W r1 = rrem & (rrem - (W)1);
         const bool two = r1 != (W)0;
-        const int w1 = two ? ctz(r1) : w0;
+        int w1 = two ? ctz(r1) : w0;
+        if constexpr (POL) {
+            if (ordered()) {
+                next_ordered(w0, w1);
+                r1 = rrem & ~bit_at<W>(w0);
+            }
+        }
         const W ho0 = row(1, w0), ho1 = row(1, w1);
         W hi0 = (W)0, hi1 = (W)0;
         if constexpr (DIR) {
@@ -610,7 +789,7 @@ struct LaneSearch {
         });
         const bool f0 = s0 > inc, f1 = two && s1 > inc;
         const bool second = two && !(f0 && f1);  // it is done as well
-        rrem = second ? r1 & (r1 - (W)1) : r1;
+        rrem = !second ? r1 : POL ? r1 & ~bit_at<W>(w1) : r1 & (r1 - (W)1);
         c_child += second ? 2u : 1u;
         c_ncls += (uint32_t)(second ? 2 * K : K);
         w = f0 ? w0 : w1;
@@ -621,7 +800,7 @@ struct LaneSearch {
     // The child (v, w) of bound b becomes the top frame: its classes with
     // both sides non-empty.  Each of them adds at least one to b, so there
     // are at most b - d - 1.  nb: where its frame starts.
-    __device__ void descend(int w, int b, int nb) {
+    __device__ __forceinline__ void descend(int w, int b, int nb) {
         const W ho = row(1, w);
         W hi = (W)0;
         if constexpr (DIR)
@@ -692,7 +871,7 @@ struct LaneSearch {
         max_used = used > max_used ? used : max_used;
     }
 
-    __device__ void step() {
+    __device__ __forceinline__ void step() {
         // pop and unmatched, in turns while lanes need them: half of the
         // unmatched children are pruned, and their lanes pop on
         for (int i = 0; i < kPops; ++i) {
@@ -717,6 +896,9 @@ struct LaneSearch {
         if (ballot(need_sel))
             if (need_sel)
                 select();
+        if constexpr (POL)
+            for (uint64_t pm = ballot(t >= 0 && (flags & (kPolV | kPolW))); pm != 0; pm &= pm - 1)
+                consult(ctz(pm));
         if (flags & kRow) {
             go = row(0, v);
             if constexpr (DIR)
@@ -778,7 +960,7 @@ struct LaneSearch {
     // Idle lanes take the lowest open frame of busy lanes, one each, from
     // the lanes whose lowest open frame is (nearly) the shallowest: a frame
     // near the leaves is gone in a few steps.
-    __device__ void steal() {
+    __device__ __forceinline__ void steal() {
         const bool is_i = t < 0;
         bool is_v = t >= 0 && lo_t < t;
         const uint32_t depth = is_v ? (uint32_t)(d - t + lo_t) : 0xFFFFu;
@@ -845,6 +1027,15 @@ struct LaneSearch {
                     if (k + i < K)
                         eput(lane, HE + k + i, wlo, x[i]);
             }
+            if (POL && ordered()) {
+                v2u64 x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    x[i] = *(glb_ptr<v2u64>)(wst + order_at(vl, d) + 16u * i);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    *(glb_ptr<v2u64>)(wst + order_at(lane, d) + 16u * i) = x[i];
+            }
             for (int j = 0; ballot(j < d) != 0; j += 32) {
                 // (up to 32 pairs in flight; past d, within the map, anything)
                 v2u64 x[4];
@@ -865,17 +1056,17 @@ struct LaneSearch {
 
     // Whether a frame below a top still has work, and where the one above it
     // starts.
-    __device__ bool open_frame(const Hdr &h) const {
+    __device__ __forceinline__ bool open_frame(const Hdr &h) const {
         return (h.r != (W)0 || ((h.y >> 24) & kUnm)) &&
                !(reprune && (int)((h.y >> 16) & 0xFFu) <= inc);
     }
-    __device__ int next_frame(int fb, const Hdr &h) const {
+    __device__ __forceinline__ int next_frame(int fb, const Hdr &h) const {
         return ((h.y >> 24) & kBig) ? cap : fb + HE + (int)((h.x >> 16) & 0xFFu);
     }
 
     // The lane's only frame, from a header's fields (K and the ring are set
     // by the caller).
-    __device__ void start_frame(int fd, uint32_t y, const W &r) {
+    __device__ __forceinline__ void start_frame(int fd, uint32_t y, const W &r) {
         t = 0;
         base = pbase = bslot = 0;
         lo_t = lo_base = 0;
@@ -889,7 +1080,7 @@ struct LaneSearch {
 
     // ---- work sharing between wavefronts ----
 
-    __device__ void raise_flag(unsigned bits) {
+    __device__ __forceinline__ void raise_flag(unsigned bits) {
         if (lane == 0) {
             if (bits & kFlagStop)
                 __hip_atomic_store(&P.g->stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -898,7 +1089,7 @@ struct LaneSearch {
                                       __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    __device__ void fail(unsigned code) {
+    __device__ __forceinline__ void fail(unsigned code) {
         if (lane == 0)
             __hip_atomic_store(&P.g->error, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         raise_flag(kFlagStop);
@@ -908,7 +1099,7 @@ struct LaneSearch {
     // The lane with the shallowest open frame below its top gives it away:
     // the lane (-1: none), the frame and its header, as scalars.  The frame
     // is not marked yet.
-    __device__ int pick_frame(int &fb, Hdr &h) {
+    __device__ __forceinline__ int pick_frame(int &fb, Hdr &h) {
         for (int tries = 0; tries < 4; ++tries) {
             const bool c = t >= 0 && lo_t < t;
             const uint32_t key = wave_min(c ? ((uint32_t)(d - t + lo_t) << 8) | (uint32_t)lane
@@ -939,7 +1130,7 @@ struct LaneSearch {
         return -1;
     }
     // Nothing is left of lane l's frame fb.
-    __device__ void gave(int l, int fb, Hdr h) {
+    __device__ __forceinline__ void gave(int l, int fb, Hdr h) {
         h.r = (W)0;
         h.y &= ~((uint32_t)kUnm << 24);
         const int lw = rl(wlo, l);
@@ -953,7 +1144,7 @@ struct LaneSearch {
     }
 
     // A free slot in ring `from`, else in the next rings.
-    __device__ bool reserve(int from, int &ring, u64w &ticket) {
+    __device__ __forceinline__ bool reserve(int from, int &ring, u64w &ticket) {
         const u64w mask = (u64w)P.ring_slots - 1;
         int ok = 0, rr = 0;
         u64w tk = 0;
@@ -984,7 +1175,7 @@ struct LaneSearch {
     }
 
     // A frame to the queue; false if there is none, or no slot is free.
-    __device__ bool donate(int to) {
+    __device__ __forceinline__ bool donate(int to) {
         int fb = 0;
         Hdr h;
         const int l = pick_frame(fb, h);
@@ -1039,7 +1230,7 @@ struct LaneSearch {
     // A frame to the waiting wavefront w of the workgroup: its classes and
     // mapping into lane 0 of that wavefront's stacks, its header into the
     // box.
-    __device__ void feed(unsigned hungry) {
+    __device__ __forceinline__ void feed(unsigned hungry) {
         wave_sync();
         int fb = 0;
         Hdr h;
@@ -1057,6 +1248,9 @@ struct LaneSearch {
         const glb_ptr<char> ws = wst + (long long)(w - wv) * P.hstack_stride;
         for (int i = lane; 4 * i < fd; i += 64)
             *(glb_ptr<u64w>)(ws + 8u * i) = *(glb_ptr<u64w>)(wst + (uint32_t)l * stride + 8u * i);
+        if (POL && fd <= P.policy_depth && lane < 8)
+            *(glb_ptr<u64w>)(ws + order_at(0, fd) + 8u * (uint32_t)lane) =
+                *(glb_ptr<u64w>)(wst + order_at(l, fd) + 8u * (uint32_t)lane);
         const uint32_t dst = at(0, HE);
         for (int i = lane; i < fK; i += 64) {
             const Ent x = eget(l, fb + HE + i, lw);
@@ -1079,7 +1273,7 @@ struct LaneSearch {
             st_wg(&T.full[w], 1u);
     }
     // The frame that a sibling has put into this wavefront's stack.
-    __device__ void accept() {
+    __device__ __forceinline__ void accept() {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         const u64w a = rl_ull(T.box[wv][0], 0);
         const int u = (int)rl_ull(T.box[wv][1], 0);
@@ -1097,7 +1291,7 @@ struct LaneSearch {
     }
     // Lane l starts on a frame of the instance whose classes and mapping are
     // in its part in HBM.
-    __device__ void begin(int l, uint32_t x, uint32_t y, const W &r) {
+    __device__ __forceinline__ void begin(int l, uint32_t x, uint32_t y, const W &r) {
         if (lane == l) {
             K = (int)((x >> 16) & 0xFFu);
             start_frame((int)(x >> 24), y, r);
@@ -1111,7 +1305,7 @@ struct LaneSearch {
     }
 
     // A unit of instance i came from outside the workgroup.
-    __device__ void new_unit(int i) {
+    __device__ __forceinline__ void new_unit(int i) {
         int u = 0;
         if (lane == 0) {
             // (one of 16 is free: each taken one has a wavefront on it)
@@ -1133,7 +1327,7 @@ struct LaneSearch {
         }
     }
     // The wavefront works on instance i from now on.
-    __device__ void enter(int i) {
+    __device__ __forceinline__ void enter(int i) {
         const DevInst di = P.inst[i];
         inst = i;
         target = sc((int)di.target);
@@ -1154,7 +1348,7 @@ struct LaneSearch {
 
     // Take a queued node into lane 0: from this XCD's ring, else from one
     // other ring, a different one on each call.
-    __device__ bool take_record() {
+    __device__ __forceinline__ bool take_record() {
         const int l = 0;
         const u64w mask = (u64w)P.ring_slots - 1;
         int ok = 0, rr = 0;
@@ -1217,12 +1411,15 @@ struct LaneSearch {
         }
         new_unit(ri);
         begin(l, ((uint32_t)rK << 16) | ((uint32_t)rd << 24), y, rr_);
+        // (a record holds no order: the scores are those it was made from)
+        if (POL && lane == l && rrem != (W)0 && ordered())
+            flags |= kPolW;
         n_pops += 1;
         return true;
     }
 
     // The next unstarted instance (its work unit was counted by the reset).
-    __device__ bool claim_instance() {
+    __device__ __forceinline__ bool claim_instance() {
         if (!roots_left)
             return false;
         int i = -1;
@@ -1261,7 +1458,7 @@ struct LaneSearch {
     }
 
     // No lane has work left.  The last wavefront to leave a unit ends it.
-    __device__ void finish_unit() {
+    __device__ __forceinline__ void finish_unit() {
         const u64w mine = count_nodes();
         if (lane == 0) {
             __hip_atomic_fetch_add(&T.nodes[unit], mine, __ATOMIC_RELAXED,
@@ -1286,7 +1483,7 @@ struct LaneSearch {
     // ---- counts ----
 
     // The nodes counted since the last call.
-    __device__ u64w count_nodes() {
+    __device__ __forceinline__ u64w count_nodes() {
         const u64w child = lanes_total(c_child), sum = child + lanes_total(c_unm);
         n_child += child;
         n_ncls += lanes_total(c_ncls);
@@ -1295,7 +1492,7 @@ struct LaneSearch {
         return sum;
     }
     // (lane 0) Nodes to the instance's count.
-    __device__ void add_nodes(u64w n) {
+    __device__ __forceinline__ void add_nodes(u64w n) {
         if (n == 0)
             return;
         a_add64(&P.nodes[inst], n);
@@ -1305,7 +1502,7 @@ struct LaneSearch {
                 raise_flag(kFlagStop);
         }
     }
-    __device__ void flush_nodes() {
+    __device__ __forceinline__ void flush_nodes() {
         const u64w n = count_nodes();
         if (lane == 0)
             add_nodes(n);
@@ -1317,7 +1514,7 @@ struct LaneSearch {
     }
 
     // Dead-end forecast (paper Sec. IV.A), as in the other kernels.
-    __device__ void forecast_dead_ends() {
+    __device__ __forceinline__ void forecast_dead_ends() {
         if (!dead_on)
             return;
         int give_up = 0;
@@ -1338,7 +1535,7 @@ struct LaneSearch {
     }
 
     // True once every P.check_ticks for one of the workgroup's wavefronts.
-    __device__ bool my_turn(unsigned *last) {
+    __device__ __forceinline__ bool my_turn(unsigned *last) {
         int mine = 0;
         if (lane == 0) {
             unsigned old = ld_wg(last);
@@ -1354,7 +1551,7 @@ struct LaneSearch {
     // Periodic.  What all XCDs share is looked at by one wavefront of the
     // workgroup at a time: lines that thousands of wavefronts read and raise
     // cost tens of microseconds each.
-    __device__ void check() {
+    __device__ __forceinline__ void check() {
         since_check = 0;
         if (rl((int)ld_wg(&T.done), 0)) {
             stop = true;
@@ -1379,8 +1576,8 @@ struct LaneSearch {
     // Limits, and frames for the rings: while workgroups of this XCD, or of
     // another one (a different one each time), are idle and their ring holds
     // fewer.
-    __device__ void look_out() {
-        const bool may_donate = !P.single_wave && P.donate_low >= 0;
+    __device__ __forceinline__ void look_out() {
+        const bool may_donate = P.donate_low >= 0;
         other = (other + 1) & (kRings - 1);
         if (other == my_ring)
             other = (other + 1) & (kRings - 1);
@@ -1428,14 +1625,14 @@ struct LaneSearch {
     // frame.  The first of the idle siblings looks at the rings meanwhile,
     // seldom while others of the workgroup are busy (they will feed it).
     // False: the search is over.
-    __device__ void count_idle(unsigned idle) {
+    __device__ __forceinline__ void count_idle(unsigned idle) {
         // (by the wavefront that looks at the rings: one at a time)
         if (lane == 0 && ld_wg(&T.idle) != idle) {
             st_wg(&T.idle, idle);
             a_add_rlx(&P.g->xcd[my_ring].idle, idle ? 1 : -1);
         }
     }
-    __device__ bool wait_work(bool share, bool claim) {
+    __device__ __forceinline__ bool wait_work(bool share, bool claim) {
         // (a sibling may write this wavefront's stack from here on: its own
         // stores there have completed)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1497,7 +1694,7 @@ struct LaneSearch {
                     raise_flag(kFlagStop);
                     break;
                 }
-                if (!P.single_wave && take_record())
+                if (take_record())
                     break;
                 gap = gap < (unsigned)P.backoff_max ? 2 * gap : gap;
                 left = alone ? gap : kFedGap * gap;
@@ -1514,9 +1711,9 @@ struct LaneSearch {
         return unit >= 0;
     }
 
-    __device__ void main_loop() {
+    __device__ __forceinline__ void main_loop() {
         t_start = now_ticks();
-        const bool share = !P.single_wave && P.donate_low >= 0;
+        const bool share = P.donate_low >= 0;
         const int check_interval = sc(P.check_interval);
         int since_steal = 0, since_feed = 0;
         u64w t_busy0 = t_start;
@@ -1595,7 +1792,7 @@ struct LaneSearch {
 
 // Up to 64 vertices a workgroup may hold a CU's 16 wavefronts (128 VGPRs);
 // wider rows take more registers, and workgroups of at most 8.
-template <typename W, bool DIR>
+template <typename W, bool DIR, bool POL>
 __global__ void __launch_bounds__(sizeof(W) <= 8 ? 1024 : 512) mcs_lane_kernel(SearchParams Pk) {
     extern __shared__ __align__(16) char smem[];
     __shared__ Team T;
@@ -1607,7 +1804,7 @@ __global__ void __launch_bounds__(sizeof(W) <= 8 ? 1024 : 512) mcs_lane_kernel(S
         T.done = 0;
         T.looked = 0;
         T.idle = 0;
-        T.left = Pk.single_wave ? 1u : blockDim.x >> 6;
+        T.left = blockDim.x >> 6;
         T.max_stack = 0;
     }
     if (threadIdx.x < kTeamStats)
@@ -1619,23 +1816,33 @@ __global__ void __launch_bounds__(sizeof(W) <= 8 ? 1024 : 512) mcs_lane_kernel(S
     }
     __syncthreads();
     const int wv = sc((int)threadIdx.x >> 6);
-    if (Pk.single_wave && (blockIdx.x != 0 || wv != 0))
-        return;
-    LaneSearch<W, DIR> s(P, T, (lds_ptr<char>)smem + (size_t)wv * (size_t)Pk.lds_per_wave, wv,
+    LaneSearch<W, DIR, POL> s(P, T, (lds_ptr<char>)smem + (size_t)wv * (size_t)Pk.lds_per_wave, wv,
                          sc((int)(blockIdx.x * (blockDim.x >> 6)) + wv));
     s.main_loop();
 }
 
 }  // namespace mcs
 
-// The kernel for rows of word_bytes (4, 8, 16 or 32), directed or not.
-extern "C" void *mcs_internal_lane_kernel(int word_bytes, int directed) {
+// The kernel for rows of word_bytes (4, 8, 16 or 32; with the learned policy
+// at most 8), directed or not.
+template <typename W>
+static void *lane_kernel(int directed, int policy) {
+    using namespace mcs;
+    if constexpr (sizeof(W) <= 8)
+        if (policy)
+            return directed ? (void *)mcs_lane_kernel<W, true, true>
+                            : (void *)mcs_lane_kernel<W, false, true>;
+    return policy     ? nullptr
+           : directed ? (void *)mcs_lane_kernel<W, true, false>
+                      : (void *)mcs_lane_kernel<W, false, false>;
+}
+extern "C" void *mcs_internal_lane_kernel(int word_bytes, int directed, int policy) {
     using namespace mcs;
     switch (word_bytes) {
-    case 4: return directed ? (void *)mcs_lane_kernel<uint32_t, true> : (void *)mcs_lane_kernel<uint32_t, false>;
-    case 8: return directed ? (void *)mcs_lane_kernel<uint64_t, true> : (void *)mcs_lane_kernel<uint64_t, false>;
-    case 16: return directed ? (void *)mcs_lane_kernel<u128, true> : (void *)mcs_lane_kernel<u128, false>;
-    case 32: return directed ? (void *)mcs_lane_kernel<u256, true> : (void *)mcs_lane_kernel<u256, false>;
+    case 4: return lane_kernel<uint32_t>(directed, policy);
+    case 8: return lane_kernel<uint64_t>(directed, policy);
+    case 16: return lane_kernel<u128>(directed, policy);
+    case 32: return lane_kernel<u256>(directed, policy);
     }
     return nullptr;
 }

@@ -88,3 +88,46 @@ def test_deep_stacks_go_on_in_the_worst_case_area(gpu, directed):
         assert r.optimal and r.size == G["n"]
         assert oracle.check.is_valid(G, H, r.mapping)
     assert st.hbm_frames > 0
+
+
+@pytest.mark.parametrize("mode", [1, 2, 3])
+@pytest.mark.parametrize("shape,directed,depth", [((28, 32, 0.2, 0.2), False, 1),
+                                                  ((28, 32, 0.2, 0.2), True, 8),
+                                                  ((33, 64, 0.1, 0.5), False, 3),
+                                                  ((33, 64, 0.1, 0.5), True, 0)])
+def test_learned_order_keeps_every_size(gpu, shape, directed, depth, mode):
+    """The learned order, whose shallow frames hold their partners' order
+    beside the stack: it changes neither the proven size nor, with the order
+    of the partners alone and the incumbent fixed, the number of nodes."""
+    from paper_1908_06418_amd import Plan
+    from paper_1908_06418_amd.policy import Policy
+    pairs, goals, counts = _case(shape, directed)
+    P = Policy(seed=31)
+    for tun in ({}, {"check_interval": 1, "donate_low": 64, "ring_slots": 64, "waves_per_cu": 1}):
+        print(f"learned lane kernel, {shape}, directed {directed}, depth {depth}, mode {mode}, "
+              f"{tun}: {len(pairs)} pairs", flush=True)
+        plan = Plan(pairs, time_limit_s=60, tuning=tun, policy=P, policy_depth=depth,
+                    policy_mode=mode).upload()
+        try:
+            plan.run()
+            assert [r.size + 1 for r in plan.results()] == goals
+            for r, (G, H) in zip(plan.results(), pairs):
+                assert r.optimal and oracle.check.is_valid(G, H, r.mapping)
+            plan.set_goals(goals)
+            plan.run()
+            res = plan.results()
+            assert all(r.optimal and r.size + 1 == g or r.size == 0 for r, g in zip(res, goals))
+            if mode == 2:
+                assert [r.nodes for r in res] == plain_counts(pairs, goals)
+        finally:
+            plan.close()
+
+
+def plain_counts(pairs, goals):
+    from paper_1908_06418_amd import Plan
+    plan = Plan(pairs, time_limit_s=60).upload()
+    plan.set_goals(goals)
+    plan.run()
+    out = [r.nodes for r in plan.results()]
+    plan.close()
+    return out
