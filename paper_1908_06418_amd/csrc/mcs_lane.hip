@@ -18,6 +18,14 @@
 // makes that part's minimum one too large: bound = d + sum instead of
 // d + 1 + sum.
 //
+// Bound: VALU issue, on batches that fill the chip.  The 4,096 pairs of 10 to
+// 35 vertices take 7 to 10 VALU instructions a node (28 with segments) and fill
+// 85 to 92% of the issue slots, 95% of the lanes holding a search; 43% of the
+// lane slots do work, since a loop over classes runs for the wavefront's
+// longest frame.  60 pairs of 30 vertices: 443 ms with segments, 93 here; 256
+// of 33: 601 and 150.  What is left of a small search is a chain of steps of
+// about 1 us: one pair of 16 vertices takes 3.6 ms with segments, 0.5 here.
+//
 // All lanes of a wavefront work on one instance, so its incumbent is a
 // scalar and its adjacency rows (up to 64 vertices) are in LDS once.
 //
@@ -67,8 +75,9 @@ constexpr int kReads = 4;
 // Idle lanes look for frames in their wavefront once there are so many, or
 // after so many steps (8 to 28 lanes: within 3%).
 constexpr int kIdleLanes = 12, kStealSteps = 8;
-// Frames may lie so much deeper than the shallowest open one to be taken.
-constexpr int kStealSpan = 9;
+// Frames may lie so much deeper than the shallowest open one to be taken, or
+// their lanes' bounds so much below the highest (steal()).
+constexpr int kStealSpan = 9, kStealBounds = 5;
 // A wavefront feeds waiting siblings once every kFeedSteps while it is rich
 // (so many lanes busy), and now and then anyway.  Feeding at every step cuts
 // the work into units of a few nodes: twice the time on small searches.
@@ -185,7 +194,7 @@ struct LaneSearch {
     int unit;            // the unit the wavefront works on, or -1
     bool stop, roots_left;
     int my_ring, steal_from, other, since_check;
-    u64w t_start, n_steps, n_don, n_pops, n_busy, n_sleep, n_big;
+    u64w t_start, n_steps, n_lanes, n_don, n_pops, n_busy, n_sleep, n_big;
     u64w n_child, n_ncls, n_pushed;
 
     __device__ LaneSearch(const KernArgs &p, Team &tm, lds_ptr<char> lds, int wave_in_block,
@@ -221,7 +230,7 @@ struct LaneSearch {
         my_ring = (int)(blockIdx.x & (kRings - 1));
         steal_from = other = my_ring;
         since_check = 0;
-        t_start = n_steps = n_don = n_pops = n_busy = n_sleep = n_big = 0;
+        t_start = n_steps = n_lanes = n_don = n_pops = n_busy = n_sleep = n_big = 0;
         n_child = n_ncls = n_pushed = 0;
     }
 
@@ -959,16 +968,24 @@ struct LaneSearch {
 
     // Idle lanes take the lowest open frame of busy lanes, one each, from
     // the lanes whose lowest open frame is (nearly) the shallowest: a frame
-    // near the leaves is gone in a few steps.
+    // near the leaves is gone in a few steps.  Undirected rows of up to 64
+    // bits: from the lanes whose top frame has (nearly) the highest bound,
+    // which finds large mappings sooner (six pairs of 30 vertices one by one 45
+    // ms by depth and 38 by bound, 4,096 of 15 to 25 34 and 25, 4,096 of 10 to 35
+    // 11 to 16 s and 9 to 18; the other kinds of pairs were slower that
+    // way: 60 directed labelled pairs 4.0 and 4.5 ms, 254 vertices 55 and 67).
     __device__ __forceinline__ void steal() {
         const bool is_i = t < 0;
         bool is_v = t >= 0 && lo_t < t;
-        const uint32_t depth = is_v ? (uint32_t)(d - t + lo_t) : 0xFFFFu;
+        constexpr bool BY_BOUND = LROWS && !DIR;
+        const uint32_t depth = !is_v      ? 0xFFFFu
+                               : BY_BOUND ? (uint32_t)(255 - bound)
+                                          : (uint32_t)(d - t + lo_t);
         const uint64_t im = ballot(is_i);
         const int ni = __builtin_popcountll(im);
         uint32_t most = wave_min(depth);
         uint64_t vm = ballot(is_v && depth <= most);
-        for (int i = 0; i < kStealSpan && __builtin_popcountll(vm) < ni; ++i)
+        for (int i = 0; i < (BY_BOUND ? kStealBounds : kStealSpan) && __builtin_popcountll(vm) < ni; ++i)
             vm = ballot(is_v && depth <= ++most);
         is_v = is_v && depth <= most;
         const int nv = __builtin_popcountll(vm);
@@ -1737,6 +1754,7 @@ struct LaneSearch {
                     steal();
                 }
             }
+            n_lanes += (unsigned)__builtin_popcountll(ballot(t >= 0));
             step();
             if (stop)
                 break;
@@ -1766,7 +1784,7 @@ struct LaneSearch {
         const int mu = (int)~wave_min(~(uint32_t)max_used);
         int last = 0;
         if (lane == 0) {
-            const u64w x[kTeamStats] = {n_steps, n_child, n_child, n_don, n_pops,
+            const u64w x[kTeamStats] = {n_steps, n_child, n_lanes, n_don, n_pops,
                                         n_busy, n_big, n_pushed, n_sleep, n_ncls};
             for (int i = 0; i < kTeamStats; ++i)
                 __hip_atomic_fetch_add(&T.st[i], x[i], __ATOMIC_RELAXED,
