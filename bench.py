@@ -36,19 +36,22 @@ PEAK_INT32_OPS = 256 * 4 * 16 * 2.4e9  # CUs x SIMDs x lanes x clock: int32 lane
 PEAK_LDS_BYTES = 256 * 128 * 2.4e9     # CUs x 128 bytes per clock x clock: LDS bytes/s
 PEAK_HBM_BYTES = 8e12
 
-# HBM bytes per launch of the search kernel, from the copy-calibrated
-# FETCH_SIZE / WRITE_SIZE runs recorded in profiles/; reported only while the
-# kernel code (comments aside, code_hash) is the one those counters were
-# taken on.
+# HBM bytes of one launch of the search kernel, from the copy-calibrated
+# FETCH_SIZE / WRITE_SIZE runs recorded in profiles/, and the nodes of those
+# launches (the parallel search order varies, and the node count with it);
+# reported, for the timed launches' nodes, only while the kernel code
+# (comments aside, code_hash) is the one those counters were taken on.
 TRAFFIC = {
-    # profiles/mcs_seg_kernel_c4.md: FETCH_SIZE 11,588,817.8 KiB x 1.9997 plus
-    # WRITE_SIZE 401,781,246.1 KiB x 1.000
-    "c4": {"source": "mcs_seg.hip", "kernel_code_hash": "4e05206b255fb045",
-           "bytes": 435_154_020_482},
-    # profiles/mcs_search_kernel_w.md: FETCH_SIZE 192,689.2 KiB x 1.9997 plus
-    # WRITE_SIZE 19,447,989.8 KiB x 1.000
-    "w": {"source": "mcs_search.hip", "kernel_code_hash": "31a3f47dc12d01c3",
-          "bytes": 20_309_302_811},
+    # profiles/mcs_lane_kernel_c4.md: FETCH_SIZE 5,431,731,007 KiB x 1.9997 in a
+    # launch of 4.692e11 nodes, WRITE_SIZE 9,718,904,245 KiB x 1.000 in one of
+    # 4.539e11
+    "c4": {"source": "mcs_lane.hip", "kernel_code_hash": "b34718448c5969a5",
+           "bytes": 21_074_674_000_000, "nodes": 461_531_919_000},
+    # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 35,698,831.4 KiB x 1.9997 in a
+    # launch of 4.999e8 nodes, WRITE_SIZE 46,421,048.1 KiB x 1.000 in one of
+    # 4.681e8
+    "w": {"source": "mcs_lane.hip", "kernel_code_hash": "b34718448c5969a5",
+          "bytes": 120_635_393_000, "nodes": 484_020_000},
 }
 
 # Algorithmic 32-bit lane operations of one matched child (v, w), per class
@@ -114,11 +117,25 @@ def kernel_hash(source: str) -> str:
     return code_hash(text)
 
 
-def traffic_for(workload: str, source: str, launches: int):
+def kernel_for(word: int, tuning: dict):
+    """Source and name of the kernel that serves rows of `word` bytes under
+    these knobs (the library's rule; no workload here has wide pairs whose
+    root bound is near their size)."""
+    seg_lanes = int(tuning.get("seg_lanes", 0) or 0)
+    if seg_lanes == 0 and int(tuning.get("stack_classes", 0) or 0) <= 0 and not (
+            word >= 16 and int(tuning.get("children_per_wave", 0) or 0) > 0):
+        return "mcs_lane.hip", "mcs_lane_kernel (a search in every lane)"
+    if word <= 8 and seg_lanes != 64:
+        return "mcs_seg.hip", f"mcs_seg_kernel ({seg_lanes or 8}-lane searches)"
+    return "mcs_search.hip", "mcs_search_kernel"
+
+
+def traffic_for(workload: str, source: str, nodes: float):
+    """HBM bytes of a launch of `nodes` nodes, or None."""
     t = TRAFFIC.get(workload)
     if not t or t.get("source") != source or t["kernel_code_hash"] != kernel_hash(source):
         return None
-    return t["bytes"] * launches
+    return t["bytes"] / t["nodes"] * nodes
 
 
 def expected_sizes(fname):
@@ -347,11 +364,7 @@ def main():
     nmax = max(max(G["n"], H["n"]) for G, H in pairs)
     word = 4 if nmax <= 32 else 8 if nmax <= 64 else 16
     directed = any(G["directed"] for G, _ in pairs)
-    seg_lanes = int(tuning.get("seg_lanes", 0) or 8)
-    segmented = word <= 8 and seg_lanes != 64
-    kernel_src = "mcs_seg.hip" if segmented else "mcs_search.hip"
-    kernel_name = (f"mcs_seg_kernel ({seg_lanes}-lane searches)" if segmented
-                   else "mcs_search_kernel")
+    kernel_src, kernel_name = kernel_for(word, tuning)
     opc = ops_per_class(word, directed)
     ops = node_classes * opc + nodes * CHILD_OPS
     kern_s = kernel_ms / 1e3
@@ -396,7 +409,7 @@ def main():
         "lds_per_wave": st.lds_per_wave,
         "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "Tops/s",
                      "frac": achieved / peak if peak else 0.0,
-                     "traffic": traffic_for(args.workload, kernel_src, 1),
+                     "traffic": traffic_for(args.workload, kernel_src, nodes / K),
                      "kernel": kernel_name,
                      "per_unit": f"{opc} int32 lane-ops per class of each matched child "
                                  f"counted as a node, plus {CHILD_OPS} per node; "

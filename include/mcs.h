@@ -97,12 +97,16 @@ typedef struct {
     int32_t donate_depth;      /* only nodes with |M| <= this are donated, as the
                                   paper delegates only above PART_LEVEL
                                   (0: any depth -- the largest min(nG, nH)) */
-    int32_t check_interval;    /* search steps between queue/limit checks (0: 128) */
+    int32_t check_interval;    /* search steps between queue/limit checks (0: 128;
+                                  with a search in every lane 4, and the
+                                  queue and the limits at most once per
+                                  10 us and workgroup) */
     int32_t no_reprune;        /* 1: do not re-test a frame's bound against the
                                   incumbent when the search returns to it */
     int32_t single_wave;       /* 1: one search alone (the first segment of one
                                   wavefront, or one wavefront with seg_lanes
-                                  64), in the sequential order: no queue, no
+                                  64, above 64 vertices or with a policy),
+                                  in the sequential order: no queue, no
                                   donations (debugging and node-count
                                   comparisons with the oracle) */
     int32_t use_graph;         /* 1: mcs_plan_run replays a HIP graph that holds
@@ -111,7 +115,8 @@ typedef struct {
                                   reset and search kernels, and the result
                                   copy back (mcs_plan_results then only waits
                                   and decodes) */
-    int32_t stack_classes;     /* segmented searches: classes of each search's
+    int32_t stack_classes;     /* > 0 chooses segmented searches (up to 64
+                                  vertices): classes of each search's
                                   stack kept in LDS (0: the worst case
                                   m(m+1)/2, m the largest min(nG, nH), or
                                   less if that keeps waves_per_cu from
@@ -126,16 +131,27 @@ typedef struct {
                                   apply to it. */
     int32_t backoff_max;       /* an idle wavefront that finds no work sleeps
                                   1, 2, 4, ... up to this many times about
-                                  3.4 us before polling again (0: 32) */
+                                  3.4 us before polling again (0: 32; with a
+                                  search in every lane 16 times about
+                                  0.3 us, and less often while other
+                                  wavefronts of the workgroup are busy) */
     int32_t seg_lanes;         /* search layout: 16, 8 or 4 -- each wavefront runs
                                   64 / seg_lanes independent searches, one per
                                   segment of that many lanes (a node's classes
                                   across the segment); 64 -- one search per
                                   wavefront, whose sibling children share the
-                                  lanes; 0: 8.  Rows of more than 64 bits and
-                                  the learned policy always use 64.  With
-                                  segments, waves_per_cu counts wavefronts
-                                  and children_per_wave is not used. */
+                                  lanes; 0: a search in every lane, which
+                                  gives way to 8 if single_wave or
+                                  stack_classes is set, and to 64 above 64
+                                  vertices or with a policy if single_wave,
+                                  children_per_wave or stack_classes is, or
+                                  above 64 vertices if some pair's Eq. 1
+                                  bound at the root is over 7/8 of its
+                                  smaller graph; mcs_solve_batch_static: 8.
+                                  Rows of more than 64 bits and the learned
+                                  policy use 64 for any other value.
+                                  waves_per_cu counts wavefronts, and
+                                  children_per_wave is used with 64 only. */
 } mcs_tuning;
 
 typedef struct {
