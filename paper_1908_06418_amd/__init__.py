@@ -68,11 +68,12 @@ _MAP_PTRS = struct.Struct("@PP")     # mcs_result.map_g, .map_h
 class _Marshal:
     """The mcs_graph arrays of a list of pairs, and the buffers behind them.
 
-    All row words of the batch go into one buffer, the labels into another: a numpy array, its ctypes pointers and a Python loop
-    over the rows of each graph took 72 ms for 4,096 pairs of 15 to 25
-    vertices, this and the plan's creation take 12.  Graphs that the flat form does not take as they are
-    (more vertices than the library allows, rows with bits above their words,
-    entries that are no integers) go one by one through _graph, which
+    All row words of the batch go into one buffer, the labels into another:
+    a numpy array, its ctypes pointers and a Python loop over the rows of each
+    graph took 72 ms for 4,096 pairs of 15 to 25 vertices, this and the
+    plan's creation take 12.  Graphs that the flat form does not take as they
+    are (more vertices than the library allows, rows with bits above their
+    words, entries that are no integers) go one by one through _graph, which
     converts or refuses them.
     """
 
