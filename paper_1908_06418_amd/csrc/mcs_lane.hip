@@ -924,7 +924,7 @@ struct LaneSearch {
             // might not fit, in the wavefront's worst-case area, if no other
             // lane is in it (a lane that has to wait takes its child back)
             int nb = base + HE + K;
-            const bool big = found && nb < cap && nb + HE + (b - d - 1) > cap;
+            const bool big = found && lane_enters_area(base, nb, HE + (b - d - 1), cap);
             const uint64_t wants = ballot(big);
             if (wants) {
                 const uint64_t owner = ballot(t >= 0 && base >= cap);

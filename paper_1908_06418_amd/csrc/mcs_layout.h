@@ -244,6 +244,13 @@ inline constexpr int lane_hdr_entries(int word_bytes) { return word_bytes == 4 ?
 inline constexpr int lane_worst_entries(int word_bytes, int m) {
     return m * (m + 1) / 2 + (m + 1) * lane_hdr_entries(word_bytes);
 }
+// Whether a child goes to the worst-case area from its lane's own part: its
+// frame would start at entry nb and take up to `need` entries; base: where its
+// parent's starts.  (A parent may end exactly where the part does: its child,
+// at cap, enters too.)
+inline constexpr bool lane_enters_area(int base, int nb, int need, int cap) {
+    return base < cap && nb + need > cap;
+}
 // LDS of a workgroup beside its wavefronts' parts (Team, at most).
 constexpr int kLaneTeamBytes = 2048;
 inline constexpr int lane_map_bytes_for(int m) { return align16(2 * (m + 1)); }
