@@ -63,6 +63,7 @@ _GRAPH = struct.Struct("@iiPP")      # mcs_graph
 _RESULT = struct.Struct("@iiPPqdd")  # mcs_result
 _MAP_AT = _abi.mcs_result.map_g.offset
 _MAP_PTRS = struct.Struct("@PP")     # mcs_result.map_g, .map_h
+_LABELS = (list, tuple, array, np.ndarray)
 
 
 class _Marshal:
@@ -73,7 +74,8 @@ class _Marshal:
     graph took 72 ms for 4,096 pairs of 15 to 25 vertices, this and the
     plan's creation take 12.  Graphs that the flat form does not take as they
     are (more vertices than the library allows, rows with bits above their
-    words, entries that are no integers) go one by one through _graph, which
+    words, entries that are no integers, labels that may be gone through only
+    once: _graph goes through them itself) go one by one through _graph, which
     converts or refuses them.
     """
 
@@ -116,6 +118,8 @@ class _Marshal:
                     words.frombytes(bytes(8 * (end - len(words))))
                 lab, lab_at = x.get("label"), -1
                 if lab is not None:
+                    if not isinstance(lab, _LABELS):
+                        raise ValueError("general path")
                     lab_at = len(labels)
                     labels.extend(lab)
                     if len(labels) == lab_at:
