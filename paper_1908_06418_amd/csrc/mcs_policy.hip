@@ -79,31 +79,36 @@ __device__ __forceinline__ v16f layer2_f32(const float *w2, int ld, const v16f h
     return acc;
 }
 
-// Scores.  Layer 2's activations are float32, its weights half precision; a
-// float32 matrix product of the layer would take twice the time of the rest,
-// so each activation is cut into two half-precision numbers, h = a + b / 2048
-// with a = half(h) and b = half(2048 (h - a)): |h - a| <= 2^-12 |h|, so what
-// is left out is at most 2^-24 |h|, float32's own rounding.  The two products
-// have accumulators of their own.  A tile with an activation beyond the half
-// range takes the float32 instructions.  Bound by the vector work around the
-// products (cutting the activations, w3).  1,000,000 rows: 31 us a call (340
-// TFLOP/s) against 1,952 us with one row per lane and float32 FMAs (5.3).
+// Scores.  Layer 2's activations are float32, its weights half precision; on
+// float32 matrix instructions the layer would take twice the time of the rest,
+// so each activation is cut into three half-precision numbers, h = a + b 2^-11
+// + c 2^-22: a = half(h) leaves at most 2^-11 |h|, b at most 2^-22 |h|, and c
+// the last bits of h's 24.  Nothing is left out: a tile with an activation of
+// which something would be (beyond the half range, or with bits below 2^-46)
+// takes the float32 instructions, and so does every tile where a weight of the
+// layer rounds to infinity (its product with a piece that is zero would be no
+// number).  The products of each piece have accumulators of their own.  Bound
+// by the vector work around the products (cutting the activations, w3).
+// 1,000,000 rows: 45 us a call (229 TFLOP/s) against 1,952 us with one row per
+// lane and float32 FMAs (5.3); with two pieces, which leave out up to 2^-23 |h|
+// and more below 2^-14, it was 31.
 __global__ void __launch_bounds__(256, 2) policy_forward_kernel(const uint16_t *X, int rows,
                                                                 const float *P, float *logits) {
     __shared__ float s2[kPolicyH * (kPolicyH + 1)];  // W2, for tiles out of the half range
-    __shared__ float s3[2 * kPolicyH];               // b2, w3
+    __shared__ float s3[3 * kPolicyH];               // b2, w3, b1
     const int lane = threadIdx.x & 63, lo = lane & 31, hi = lane >> 5;
     for (int i = threadIdx.x; i < kPolicyH * kPolicyH; i += blockDim.x)
         s2[(i / kPolicyH) * (kPolicyH + 1) + i % kPolicyH] = round_half(P[kOffW2 + i]);
-    for (int i = threadIdx.x; i < 2 * kPolicyH; i += blockDim.x)
-        s3[i] = round_half(i < kPolicyH ? P[kOffB2 + i] : P[kOffW3 + i - kPolicyH]);
+    for (int i = threadIdx.x; i < kPolicyH; i += blockDim.x) {
+        s3[i] = round_half(P[kOffB2 + i]);
+        s3[kPolicyH + i] = round_half(P[kOffW3 + i]);
+        s3[2 * kPolicyH + i] = round_half(P[kOffB1 + i]);
+    }
     __syncthreads();
     v8h w1[2], w2[2][4];
-    v16f b1[2];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         w1[m] = load_w1(P, m, lo, hi);
-        b1[m] = load_units(P + kOffB1, m, hi);
         // chunk c contracts units 16 c .. + 15, in the order in which the
         // two half-wavefronts hold them
 #pragma unroll
@@ -114,33 +119,49 @@ __global__ void __launch_bounds__(256, 2) policy_forward_kernel(const uint16_t *
                                            acc_unit(8 * (c & 1) + i, hi)];
     }
     const float b3 = round_half(P[kOffB3]);
+    float sum2 = 0.f;  // 0, or NaN if a weight of layer 2 is no finite number
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                sum2 += 0.f * (float)w2[m][c][i];
+    const bool finite = __ballot(sum2 != 0.f) == 0;
     const int tiles = (rows + 31) / 32, step = gridDim.x * (blockDim.x >> 6);
     for (int tile = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); tile < tiles;
          tile += step) {
         const int row = 32 * tile + lo;
         const v8h x = load_x(X, row, rows, hi);
+        asm volatile("" ::: "memory");  // (b1, b2 and w3 stay in LDS between tiles)
         v16f h[2];
-        float most = 0.f;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            h[m] = layer1(w1[m], x, b1[m]);
+            v16f b1;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < 16; ++r)
+                b1[r] = s3[2 * kPolicyH + 32 * m + acc_unit(r, hi)];
+            h[m] = layer1(w1[m], x, b1);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
                 h[m][r] = fmaxf(h[m][r], 0.f);
-                most = fmaxf(most, h[m][r]);
-            }
         }
         float z = 0.f;
-        if (__ballot(!(most < 65000.f)) == 0) {
-            v8h a[4], b[4];
+        v8h a[4], b[4], c[4];
+        uint32_t left = 0;  // not 0: some activation is more than its pieces
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float v = h[c >> 1][8 * (c & 1) + i];
-                    a[c][i] = (_Float16)v;
-                    b[c][i] = (_Float16)((v - (float)a[c][i]) * 2048.f);
-                }
+            for (int i = 0; i < 8; ++i) {
+                const float v = h[q >> 1][8 * (q & 1) + i];
+                a[q][i] = (_Float16)v;
+                const float vb = (v - (float)a[q][i]) * 2048.f;
+                b[q][i] = (_Float16)vb;
+                const float vc = (vb - (float)b[q][i]) * 2048.f;
+                c[q][i] = (_Float16)vc;
+                left |= __float_as_uint(vc - (float)c[q][i]);
+            }
+        if (finite && __ballot(left != 0) == 0) {
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 v16f acc, low = {};
@@ -148,9 +169,15 @@ __global__ void __launch_bounds__(256, 2) policy_forward_kernel(const uint16_t *
                 for (int r = 0; r < 16; ++r)
                     acc[r] = s3[32 * m + acc_unit(r, hi)];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2[m][c], a[c], acc, 0, 0, 0);
-                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2[m][c], b[c], low, 0, 0, 0);
+                for (int q = 0; q < 4; ++q)
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2[m][q], c[q], low, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    low[r] *= 1.f / 2048.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2[m][q], a[q], acc, 0, 0, 0);
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2[m][q], b[q], low, 0, 0, 0);
                 }
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
