@@ -61,6 +61,7 @@
 // wavefront, however many of its lanes work on it.
 #include "mcs_device.h"
 #include "mcs_policy.h"
+#include "mcs_team.h"
 
 namespace mcs {
 
@@ -118,32 +119,22 @@ using KernArgs = __attribute__((address_space(4))) SearchParams;
 // Lane `from`'s x (every lane of the wavefront active).
 DEV int shfl_any(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
 
-// What the wavefronts of a workgroup share.
-constexpr int kTeamStats = 10;
-struct Team {
-    unsigned hungry;      // bit w: wavefront w waits for a frame
-    unsigned done;        // the search is over
-    unsigned looked;      // ticks of the last look at the rings (low word)
-    unsigned idle;        // 1: the workgroup is counted as idle
-    unsigned full[16];    // 1: a frame for wavefront w is in its stack, its
-    u64w box[16][6];      //    header here (x, y; unit; partners)
-    // work units: one instance each, on one or more of the wavefronts
-    unsigned ref[16];     // 0: free; 1 + the wavefronts on it
-    int inst[16];
-    int inc[16];          // the incumbent as last seen or raised
-    unsigned seen[16];    // ticks of the last look at it
-    u64w nodes[16];       // counted by wavefronts that have left
-    unsigned left;        // wavefronts that have not ended
-    int max_stack;
-    u64w st[kTeamStats];  // the wavefronts' statistics
-};
-static_assert(sizeof(Team) <= kLaneTeamBytes, "the host leaves room for it in LDS");
 template <typename T>
 DEV T ld_wg(T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 template <typename T>
 DEV void st_wg(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+struct WgOps {
+    template <typename T>
+    DEV T add(T *p, T x) {
+        return __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    template <typename T>
+    DEV T swap(T *p, T x) {
+        return __hip_atomic_exchange(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
 
 }  // namespace
 
@@ -1478,12 +1469,9 @@ struct LaneSearch {
     __device__ __forceinline__ void finish_unit() {
         const u64w mine = count_nodes();
         if (lane == 0) {
-            __hip_atomic_fetch_add(&T.nodes[unit], mine, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (__hip_atomic_fetch_add(&T.ref[unit], ~0u, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP) == 2u) {
-                add_nodes(__hip_atomic_exchange(&T.nodes[unit], 0ull, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_WORKGROUP));
+            u64w total = 0;
+            if (team_leave<WgOps>(T, unit, mine, &total)) {
+                add_nodes(total);
                 if (!stop) {
                     if (a_add_rlx(&P.open[inst], -1) == 1)
                         __hip_atomic_store(&P.t_proof[inst], now_ticks(), __ATOMIC_RELAXED,
@@ -1778,8 +1766,7 @@ struct LaneSearch {
             n_busy += now_ticks() - t_busy0;
             const u64w n = count_nodes();
             if (lane == 0)
-                add_nodes(n + __hip_atomic_exchange(&T.nodes[unit], 0ull, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP));
+                team_stop<WgOps>(T, unit, n);
         }
         const int mu = (int)~wave_min(~(uint32_t)max_used);
         int last = 0;
@@ -1798,6 +1785,11 @@ struct LaneSearch {
             // the workgroup's last wavefront hands in its sums
             static_assert(offsetof(SearchStats, node_classes) == 8 * kTeamStats, "in this order");
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (lane < 16) {
+                const u64w n = team_rest<WgOps>(T, lane);
+                if (n != 0)
+                    a_add64(&P.nodes[T.inst[lane]], n);
+            }
             SearchStats *g = &P.g->st[my_ring];
             if (lane < kTeamStats)
                 a_add64(&g->batches + lane, T.st[lane]);
