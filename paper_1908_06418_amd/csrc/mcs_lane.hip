@@ -1631,10 +1631,11 @@ struct LaneSearch {
     // seldom while others of the workgroup are busy (they will feed it).
     // False: the search is over.
     __device__ __forceinline__ void count_idle(unsigned idle) {
-        // (by the wavefront that looks at the rings: one at a time)
-        if (lane == 0 && ld_wg(&T.idle) != idle) {
-            st_wg(&T.idle, idle);
-            a_add_rlx(&P.g->xcd[my_ring].idle, idle ? 1 : -1);
+        // (two of them may look at the rings, and take work, at the same time)
+        if (lane == 0) {
+            const int change = team_idle<WgOps>(T, idle);
+            if (change != 0)
+                a_add_rlx(&P.g->xcd[my_ring].idle, change);
         }
     }
     __device__ __forceinline__ bool wait_work(bool share, bool claim) {
@@ -1688,8 +1689,8 @@ struct LaneSearch {
                 }
                 if (over)
                     break;
-                if (share && alone)
-                    count_idle(1);
+                if (share)
+                    count_idle(alone ? 1 : 0);
                 unsigned fl = 0;
                 if (lane == 0)
                     fl = ld_rlx(&P.g->xcd[my_ring].flag);
@@ -1710,7 +1711,7 @@ struct LaneSearch {
         }
         if (fed)
             accept();
-        else if (unit >= 0)
+        if (unit >= 0)
             count_idle(0);
         n_sleep += now_ticks() - t_sleep;
         return unit >= 0;

@@ -50,5 +50,11 @@ template <class Ops>
 [[gnu::always_inline]] constexpr unsigned long long team_rest(Team &T, int unit) {
     return Ops::swap(&T.nodes[unit], 0ull);
 }
+// Whether the workgroup is without work, said by any of its wavefronts: what to
+// add to its XCD's count.
+template <class Ops>
+[[gnu::always_inline]] constexpr int team_idle(Team &T, unsigned idle) {
+    return (int)idle - (int)Ops::swap(&T.idle, idle);
+}
 
 }  // namespace mcs

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <thread>
 #include <vector>
 
 #include "mcs_team.h"
@@ -17,6 +18,30 @@ struct Ops {
         return __atomic_exchange_n(p, x, __ATOMIC_RELAXED);
     }
 };
+
+// Four wavefronts that say at once, again and again, whether there is work:
+// the changes they hand in sum to what was said last.
+static int idle_counts() {
+    int bad = 0;
+    for (int round = 0; round < 20; round++) {
+        mcs::Team T;
+        std::memset(&T, 0, sizeof T);
+        long long count = 0;
+        std::vector<std::thread> ws;
+        for (unsigned w = 0; w < 4; w++)
+            ws.emplace_back([&, w] {
+                unsigned x = 12345u + w;
+                for (int i = 0; i < 100000; i++) {
+                    x = x * 1664525u + 1013904223u;
+                    Ops::add(&count, (long long)mcs::team_idle<Ops>(T, x >> 31));
+                }
+            });
+        for (std::thread &t : ws)
+            t.join();
+        bad += count != (long long)T.idle;
+    }
+    return bad;
+}
 
 int main() {
     int orders = 0, bad = 0;
@@ -50,6 +75,8 @@ int main() {
             bad += in != sum || ended != (stops == 0);
         } while (std::next_permutation(ord.begin(), ord.end()));
     }
-    std::printf("orders %d bad %d\n", orders, bad);
+    const int miscounted = idle_counts();
+    std::printf("orders %d bad %d idle %d\n", orders, bad, miscounted);
+    bad += miscounted;
     return bad != 0;
 }

@@ -1,5 +1,6 @@
 """What the lane kernel's wavefronts share in a workgroup (mcs_team.h), on the
-CPU: nodes of a stopped unit are handed in once, whoever leaves last."""
+CPU: nodes of a stopped unit are handed in once, whoever leaves last, and a
+workgroup is counted as idle once, whoever says so."""
 import os
 import shutil
 import subprocess
@@ -10,15 +11,15 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 
-def test_nodes_of_a_stopped_unit_are_handed_in(tmp_path):
+def test_transitions_of_a_team(tmp_path):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("needs g++")
     exe = str(tmp_path / "team")
-    r = subprocess.run([gxx, "-O1", "-std=c++17", "-I",
+    r = subprocess.run([gxx, "-O1", "-std=c++17", "-pthread", "-I",
                         os.path.join(ROOT, "paper_1908_06418_amd", "csrc"),
                         os.path.join(HERE, "lane_model", "team.cpp"), "-o", exe],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-4000:]
     r = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=60)
-    assert r.returncode == 0 and "orders 384 bad 0" in r.stdout, r.stdout
+    assert r.returncode == 0 and "orders 384 bad 0 idle 0" in r.stdout, r.stdout
