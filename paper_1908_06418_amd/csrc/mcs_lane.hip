@@ -1399,6 +1399,10 @@ struct LaneSearch {
         const uint32_t y = sc((uint32_t)rh.v | ((uint32_t)rh.sel << 8) |
                               ((uint32_t)rh.bound << 16) | ((uint32_t)rh.flags << 24));
         const W rr_ = sc((W)rh.rrem);
+        if (!record_fits(ri, rK, rd, P.count, P.frames)) {
+            fail(kErrRecord);  // (a broken invariant: no such frame)
+            return false;
+        }
         // the record's words go straight to lane l's stack
         u64w *rmap = (u64w *)(slot + rec_map_off<W>());
         for (int i = lane; 4 * i < rd; i += 64)
@@ -1413,10 +1417,6 @@ struct LaneSearch {
         if (lane == 0)
             st_rlx(&P.seq[idx], hd + (u64w)P.ring_slots);
         wave_sync();
-        if (ri >= P.count || rK > P.frames || rd >= P.frames) {
-            fail(kErrRecord);  // (a broken invariant: no such frame)
-            return false;
-        }
         new_unit(ri);
         begin(l, ((uint32_t)rK << 16) | ((uint32_t)rd << 24), y, rr_);
         // (a record holds no order: the scores are those it was made from)

@@ -251,6 +251,12 @@ inline constexpr int lane_worst_entries(int word_bytes, int m) {
 inline constexpr bool lane_enters_area(int base, int nb, int need, int cap) {
     return base < cap && nb + need > cap;
 }
+// Whether a record is a frame that a lane's part of the stack has room for:
+// frames is m + 1, for the largest m of the launch's count instances, and a
+// part holds a header and m classes at least.
+inline constexpr bool record_fits(int inst, int K, int d, int count, int frames) {
+    return inst >= 0 && inst < count && K < frames && d < frames;
+}
 // LDS of a workgroup beside its wavefronts' parts (Team, at most).
 constexpr int kLaneTeamBytes = 2048;
 inline constexpr int lane_map_bytes_for(int m) { return align16(2 * (m + 1)); }
