@@ -2,6 +2,7 @@
 // at the smallest part that the host lays out, and every frame of a search
 // is taken.
 #include <cstdio>
+#include <initializer_list>
 
 #include "mcs_layout.h"
 
