@@ -122,8 +122,9 @@ def kernel_for(word: int, tuning: dict):
     these knobs (the library's rule; no workload here has wide pairs whose
     root bound is near their size)."""
     seg_lanes = int(tuning.get("seg_lanes", 0) or 0)
-    if seg_lanes == 0 and int(tuning.get("stack_classes", 0) or 0) <= 0 and not (
-            word >= 16 and int(tuning.get("children_per_wave", 0) or 0) > 0):
+    knob = lambda k: int(tuning.get(k, 0) or 0)  # noqa: E731
+    if seg_lanes == 0 and knob("stack_classes") <= 0 and not knob("single_wave") and \
+            knob("donate_low") >= 0 and not (word >= 16 and knob("children_per_wave") > 0):
         return "mcs_lane.hip", "mcs_lane_kernel (a search in every lane)"
     if word <= 8 and seg_lanes != 64:
         return "mcs_seg.hip", f"mcs_seg_kernel ({seg_lanes or 8}-lane searches)"

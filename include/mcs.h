@@ -142,9 +142,10 @@ typedef struct {
                                   wavefront, whose sibling children share the
                                   lanes; 0: a search in every lane, which
                                   gives way to 8 if single_wave or
-                                  stack_classes is set, and to 64 above 64
-                                  vertices or with a policy if single_wave,
-                                  children_per_wave or stack_classes is, or
+                                  stack_classes is set or donate_low < 0,
+                                  and to 64 above 64 vertices or with a
+                                  policy in these cases and if
+                                  children_per_wave is set, or
                                   above 64 vertices if some pair's Eq. 1
                                   bound at the root is over 7/8 of its
                                   smaller graph; mcs_solve_batch_static: 8.

@@ -645,11 +645,15 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         for (int i = 0; wide && i < ndev; i++)
             deep = deep || 8 * p->root_bound[i] > 7 * p->m[i];
         // One search alone is a single lane there, 1.1 us a node against 0.65
-        // on a segment and less on a wavefront.  The learned policy goes with
+        // on a segment and less on a wavefront.  A launch that never
+        // donates keeps each instance on the lane that it starts on (64 pairs
+        // of 24 vertices 6.5 s, and 3.1 on segments, eight to a wavefront; 24
+        // directed labelled pairs of 70 to 90 2.7, and 0.7 with a search per
+        // wavefront).  The learned policy goes with
         // it: 24 pairs of 28 vertices take 152 ms with a search per wavefront
         // and 34 with one per lane.
         p->lane = may_lane && sl == 0 && p->tun.stack_classes <= 0 && !deep &&
-                  !p->tun.single_wave &&
+                  !p->tun.single_wave && p->tun.donate_low >= 0 &&
                   !((wide || p->policy) && p->tun.children_per_wave > 0);
         if (p->lane)
             p->seg_log = 0;

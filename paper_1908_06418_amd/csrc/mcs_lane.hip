@@ -1582,7 +1582,6 @@ struct LaneSearch {
     // another one (a different one each time), are idle and their ring holds
     // fewer.
     __device__ __forceinline__ void look_out() {
-        const bool may_donate = P.donate_low >= 0;
         other = (other + 1) & (kRings - 1);
         if (other == my_ring)
             other = (other + 1) & (kRings - 1);
@@ -1606,8 +1605,6 @@ struct LaneSearch {
             stop = true;
             return;
         }
-        if (!may_donate)
-            return;
         const long long waiting = (long long)(rl_ull(x, 1) - rl_ull(x, 2));
         const long long waiting_o = (long long)(rl_ull(x, 4) - rl_ull(x, 5));
         const int idle = (int)(ctl >> 32), idle_o = (int)(rl_ull(x, 3) >> 32);
@@ -1638,7 +1635,7 @@ struct LaneSearch {
                 a_add_rlx(&P.g->xcd[my_ring].idle, change);
         }
     }
-    __device__ __forceinline__ bool wait_work(bool share, bool claim) {
+    __device__ __forceinline__ bool wait_work(bool claim) {
         // (a sibling may write this wavefront's stack from here on: its own
         // stores there have completed)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1653,7 +1650,7 @@ struct LaneSearch {
                 continue;
             }
             if (!first) {
-                if (share && !listed) {
+                if (!listed) {
                     if (lane == 0)
                         __hip_atomic_fetch_or(&T.hungry, bit, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1668,29 +1665,26 @@ struct LaneSearch {
                 const unsigned hungry = (unsigned)rl((int)ld_wg(&T.hungry), 0);
                 if (left != 0)
                     left -= 1;
-                if (share && hungry == all && left > gap)
+                if (hungry == all && left > gap)
                     left = gap;
-                if (!over && (left != 0 || (share && (hungry & (bit - 1u)) != 0)))
+                if (!over && (left != 0 || (hungry & (bit - 1u)) != 0))
                     continue;
-                const bool alone = !share || hungry == all;  // nobody here can feed it
-                if (listed) {
-                    unsigned old = 0;
-                    if (lane == 0)
-                        old = __hip_atomic_fetch_and(&T.hungry, ~bit, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-                    listed = false;
-                    if (!((unsigned)rl((int)old, 0) & bit)) {
-                        // a sibling has taken the bit off: its frame is on its way
-                        while (!rl((int)ld_wg(&T.full[wv]), 0))
-                            __builtin_amdgcn_s_sleep(2);
-                        fed = true;
-                        break;
-                    }
+                const bool alone = hungry == all;  // nobody here can feed it
+                unsigned old = 0;
+                if (lane == 0)
+                    old = __hip_atomic_fetch_and(&T.hungry, ~bit, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+                listed = false;
+                if (!((unsigned)rl((int)old, 0) & bit)) {
+                    // a sibling has taken the bit off: its frame is on its way
+                    while (!rl((int)ld_wg(&T.full[wv]), 0))
+                        __builtin_amdgcn_s_sleep(2);
+                    fed = true;
+                    break;
                 }
                 if (over)
                     break;
-                if (share)
-                    count_idle(alone ? 1 : 0);
+                count_idle(alone ? 1 : 0);
                 unsigned fl = 0;
                 if (lane == 0)
                     fl = ld_rlx(&P.g->xcd[my_ring].flag);
@@ -1719,7 +1713,6 @@ struct LaneSearch {
 
     __device__ __forceinline__ void main_loop() {
         t_start = now_ticks();
-        const bool share = P.donate_low >= 0;
         const int check_interval = sc(P.check_interval);
         int since_steal = 0, since_feed = 0;
         u64w t_busy0 = t_start;
@@ -1732,11 +1725,11 @@ struct LaneSearch {
                     finish_unit();
                     n_busy += now_ticks() - t_busy0;
                 }
-                if (!wait_work(share, claim))
+                if (!wait_work(claim))
                     break;
                 claim = true;
                 t_busy0 = now_ticks();
-            } else if (am != ~0ull && share) {
+            } else if (am != ~0ull) {
                 const int idle = 64 - __builtin_popcountll(am);
                 if (idle >= kIdleLanes || ++since_steal >= kStealSteps) {
                     since_steal = 0;
@@ -1747,7 +1740,7 @@ struct LaneSearch {
             step();
             if (stop)
                 break;
-            if (share && ++since_feed >= kFeedSteps &&
+            if (++since_feed >= kFeedSteps &&
                 (__builtin_popcountll(ballot(t >= 0)) >= kFeedRich || since_feed >= kFeedAnyway)) {
                 const unsigned hungry = (unsigned)rl((int)ld_wg(&T.hungry), 0);
                 if (hungry) {
