@@ -148,7 +148,10 @@ typedef struct {
                                   children_per_wave is set, or
                                   above 64 vertices if some pair's Eq. 1
                                   bound at the root is over 7/8 of its
-                                  smaller graph; mcs_solve_batch_static: 8.
+                                  smaller graph; and to 8 (64 with a policy)
+                                  above 32 vertices if all pairs' bounds are
+                                  and their graphs have (nearly) the same
+                                  degrees; mcs_solve_batch_static: 8.
                                   Rows of more than 64 bits and the learned
                                   policy use 64 for any other value.
                                   waves_per_cu counts wavefronts, and

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -146,14 +147,35 @@ mcs_status validate(const mcs_graph &g, const char *which, int idx) {
     return MCS_OK;
 }
 
-// Descending degree (out + in when directed), ties by index (Sec. IV.A).
-std::vector<int> degree_order(const mcs_graph &g) {
-    std::vector<int> deg(g.n, 0), ord(g.n);
+// Degrees (out + in when directed).
+std::vector<int> degrees(const mcs_graph &g) {
+    std::vector<int> deg(g.n, 0);
     for_arcs(g, [&](int i, int j) {
         deg[i]++;
         if (g.directed)
             deg[j]++;
     });
+    return deg;
+}
+
+// Whether the graphs have the same degrees but for n / 8 in sum, as a graph
+// and its relabelled copy have, or one with an edge or two changed.
+bool like_copies(const mcs_graph &g, const mcs_graph &h) {
+    if (g.n != h.n)
+        return false;
+    std::vector<int> a = degrees(g), b = degrees(h);
+    std::sort(a.begin(), a.end());
+    std::sort(b.begin(), b.end());
+    int apart = 0;
+    for (int i = 0; i < g.n; i++)
+        apart += std::abs(a[i] - b[i]);
+    return 8 * apart <= g.n;
+}
+
+// Descending degree, ties by index (Sec. IV.A).
+std::vector<int> degree_order(const mcs_graph &g) {
+    const std::vector<int> deg = degrees(g);
+    std::vector<int> ord(g.n);
     for (int i = 0; i < g.n; i++)
         ord[i] = i;
     std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return deg[a] > deg[b]; });
@@ -632,18 +654,34 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         else
             p->seg_log = sl == 4 ? 2 : sl == 16 ? 4 : 3;  // unless seg_lanes says: 8 lanes
         // The default is a search in every lane (mcs_lane.hip), unless a knob
-        // of another kernel is set.  With wide rows only if no instance can
-        // dive deep: a frame of close to n classes is one long loop of a
-        // lane but a few steps of a wavefront, and an instance whose Eq. 1
-        // bound at the root is near its size (unlabelled graphs, relabelled
-        // copies) may have to go through n of them one after another (eight
-        // pairs of a graph of 129 to 254 vertices and its copy: 2.5 ms with a
-        // search per wavefront, 71 ms with one per lane).  Random labelled
-        // pairs have root bounds of about 0.5 to 0.8 of their size and
-        // frames of ten to twenty classes.
+        // of another kernel is set, or the instances dive deep: a frame of
+        // close to n classes is one long loop of a lane but a few steps of a
+        // wavefront, and an instance whose Eq. 1 bound at the root is near its
+        // size may have to go through n of them one after another.  Wide rows:
+        // if any instance's bound is (eight pairs of a graph of 129 to 254
+        // vertices and its copy: 2.5 ms with a search per wavefront, 71 ms
+        // with one per lane); random labelled pairs have bounds of about 0.5
+        // to 0.8 of their size and frames of ten to twenty classes.  64-bit
+        // rows: if all are near copies as well, since random unlabelled pairs
+        // have that bound too and run 4 to 8 times as fast here (8 pairs of a
+        // 64-vertex graph and its copy: 2.0 ms on segments, 4.8 with one per
+        // lane; one edge of the copies changed 2.6 and 4.5; 40 vertices 1.2
+        // and 1.9, two edges changed 2.0 and 8.1; two edgeless graphs 1.1 and
+        // 2.2).  Copies of up to 32 vertices are over sooner here (1.5 and
+        // 0.9).
         bool deep = false;
-        for (int i = 0; wide && i < ndev; i++)
-            deep = deep || 8 * p->root_bound[i] > 7 * p->m[i];
+        if (p->word_bytes >= 8) {
+            auto near = [&](int i) { return 8 * p->root_bound[i] > 7 * p->m[i]; };
+            bool any = false, all = true;
+            for (int i = 0; i < ndev; i++) {
+                const bool d = near(i);
+                any = any || d;
+                all = all && d;
+            }
+            for (int k = 0; !wide && all && k < count; k++)
+                all = like_copies(G[k], H[k]);
+            deep = wide ? any : all;
+        }
         // One search alone is a single lane there, 1.1 us a node against 0.65
         // on a segment and less on a wavefront.  A launch that never
         // donates keeps each instance on the lane that it starts on (64 pairs
