@@ -151,7 +151,9 @@ typedef struct {
                                   smaller graph; and to 8 (64 with a policy)
                                   above 32 vertices if all pairs' bounds are
                                   and their graphs have (nearly) the same
-                                  degrees; mcs_solve_batch_static: 8.
+                                  degrees; and to 64 with a policy deeper
+                                  than 3 (it picks v), 4 (it orders w) or 2
+                                  (both); mcs_solve_batch_static: 8.
                                   Rows of more than 64 bits and the learned
                                   policy use 64 for any other value.
                                   waves_per_cu counts wavefronts, and

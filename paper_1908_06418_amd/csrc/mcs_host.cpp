@@ -410,6 +410,9 @@ void pack_word(std::vector<uint8_t> &buf, int word_bytes, const Bits &x) {
     pack_word(buf.data() + at, word_bytes, x);
 }
 
+// The deepest learned order that the lane kernel takes.
+int lane_policy_depth(int mode) { return mode == 1 ? 3 : mode == 2 ? 4 : 2; }
+
 int next_pow2(int x) {
     int p = 1;
     while (p < x)
@@ -687,12 +690,18 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         // donates keeps each instance on the lane that it starts on (64 pairs
         // of 24 vertices 6.5 s, and 3.1 on segments, eight to a wavefront; 24
         // directed labelled pairs of 70 to 90 2.7, and 0.7 with a search per
-        // wavefront).  The learned policy goes with
-        // it: 24 pairs of 28 vertices take 152 ms with a search per wavefront
-        // and 34 with one per lane.
+        // wavefront).  The learned policy goes with it (24 pairs of 28
+        // vertices, depth 1: 138 ms with a search per wavefront and 30 with
+        // one per lane) down to the depth where most of the time goes to the
+        // scores, which a wavefront computes for one lane at a time there: 12
+        // pairs of 26 vertices 78 and 51 ms at depth 3, 104 and 101 at 4, 124
+        // and 148 at 6 for the partners' order; v's choice 73 and 59 at 3,
+        // 106 and 132 at 4; both 70 and 34 at 2, 119 and 111 at 3 (512 pairs
+        // of 16 to 20 94 and 109), 193 and 256 at 4.
         p->lane = may_lane && sl == 0 && p->tun.stack_classes <= 0 && !deep &&
                   !p->tun.single_wave && p->tun.donate_low >= 0 &&
-                  !((wide || p->policy) && p->tun.children_per_wave > 0);
+                  !((wide || p->policy) && p->tun.children_per_wave > 0) &&
+                  !(p->policy && p->policy_depth > lane_policy_depth(p->policy_mode));
         if (p->lane)
             p->seg_log = 0;
     }

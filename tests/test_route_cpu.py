@@ -49,3 +49,20 @@ def test_copies_of_more_than_32_vertices_are_not_for_one_search_in_every_lane(mc
     from paper_1908_06418_amd import workspace_size
     segments = workspace_size(pairs, tuning={"seg_lanes": 8})
     assert (workspace_size(pairs) != segments) is lane
+
+
+@pytest.mark.parametrize("mode,deepest", [(1, 3), (2, 4), (3, 2)])
+def test_deep_learned_orders_are_not_for_one_search_in_every_lane(mcs_lib, mode, deepest):
+    import ctypes
+
+    import torch
+
+    from paper_1908_06418_amd import _Marshal, _opts
+    params = torch.zeros(6000, dtype=torch.float16)  # (only its address is taken)
+    aligned = params[(-params.data_ptr() % 16) // 2:]
+    m = _Marshal(SMALL)
+    for depth in range(9):
+        size = [int(mcs_lib.mcs_workspace_size(len(SMALL), m.G, m.H, ctypes.byref(
+            _opts(0, 0, tun, policy=aligned, policy_depth=depth, policy_mode=mode)[0])))
+            for tun in (None, {"seg_lanes": 64})]
+        assert (size[0] != size[1]) is (depth <= deepest)
