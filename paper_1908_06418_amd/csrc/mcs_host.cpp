@@ -18,6 +18,9 @@
 
 extern "C" void *mcs_internal_search_kernel(int word_bytes, int directed, int policy);
 extern "C" void *mcs_internal_seg_kernel(int word_bytes, int directed, int seg_log);
+// (weak: a host-only build of the plan code links without the lane kernel)
+extern "C" __attribute__((weak)) void *mcs_internal_lane_kernel(int word_bytes, int directed,
+                                                                int policy);
 extern "C" void *mcs_internal_static_scratch(size_t *bytes, int *err);
 extern "C" void *mcs_internal_reset_kernel(void);
 
@@ -439,15 +442,17 @@ const char *mcs_status_string(mcs_status s) {
 
 const char *mcs_last_error(void) { return g_err.c_str(); }
 
-// may_lane: the kernel with a search in every lane may be chosen (the
-// static-scratch entry keeps the kernels whose stacks fit there).
 static void *search_fn(const mcs_plan *p) {
     if (p->lane)
-        return mcs_internal_seg_kernel(p->word_bytes, p->directed, p->policy ? -1 : 0);
+        return mcs_internal_lane_kernel
+                   ? mcs_internal_lane_kernel(p->word_bytes, p->directed, p->policy != nullptr)
+                   : nullptr;
     return p->seg_log ? mcs_internal_seg_kernel(p->word_bytes, p->directed, p->seg_log)
                       : mcs_internal_search_kernel(p->word_bytes, p->directed, p->policy != nullptr);
 }
 
+// may_lane: the kernel with a search in every lane may be chosen (the
+// static-scratch entry keeps the kernels whose stacks fit there).
 static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph *H,
                               const mcs_opts *opts, mcs_plan **out, bool may_lane) {
     g_err.clear();

@@ -1272,17 +1272,11 @@ __global__ void __launch_bounds__(256) mcs_seg_kernel(SearchParams Pk) {
 
 }  // namespace mcs
 
-extern "C" void *mcs_internal_lane_kernel(int word_bytes, int directed, int policy);
-
 // Launch entry point used by the host driver: the kernel for rows of
 // word_bytes (4 or 8), directed or not, with segments of 2^seg_log lanes
-// (2, 3 or 4); with seg_log 0, the kernel with a search in every lane, for
-// rows of 4 to 32 bytes, with seg_log -1 that kernel with the learned policy;
-// null for anything else.
+// (2, 3 or 4); null for anything else.
 extern "C" void *mcs_internal_seg_kernel(int word_bytes, int directed, int seg_log) {
     using namespace mcs;
-    if (seg_log <= 0)
-        return mcs_internal_lane_kernel(word_bytes, directed, seg_log == -1);
     if (seg_log == 2)
         return word_bytes == 4 ? (directed ? (void *)mcs_seg_kernel<uint32_t, true, 2>
                                            : (void *)mcs_seg_kernel<uint32_t, false, 2>)
