@@ -315,7 +315,7 @@ mcs_status mcs_solve_batch(int32_t count, const mcs_graph *G, const mcs_graph *H
                            const mcs_opts *opts, void *workspace, size_t bytes,
                            void *stream, mcs_result *results);
 
-/* Bytes of the library's static device scratch (64 MiB). */
+/* Bytes of the library's static device scratch (64 MiB; it holds 2 KiB more). */
 #define MCS_STATIC_SCRATCH_BYTES (64u << 20)
 
 /* For callers that cannot allocate device memory -- code under HIP graph
@@ -332,7 +332,8 @@ mcs_status mcs_solve_batch(int32_t count, const mcs_graph *G, const mcs_graph *H
  * overlap on one device (other host threads, other streams) race on the
  * scratch: serialize them.  Synchronous on stream.  Errors: as
  * mcs_solve_batch; MCS_E_WORKSPACE if the batch needs more than
- * MCS_STATIC_SCRATCH_BYTES (mcs_workspace_size tells; fewer wavefronts per
+ * MCS_STATIC_SCRATCH_BYTES (mcs_workspace_size tells, with seg_lanes 8 where
+ * it is 0: this entry never runs a search in every lane; fewer wavefronts per
  * CU or one search per wavefront need less); MCS_E_INVALID for use_graph;
  * MCS_E_DEVICE if the scratch's address cannot be looked up. */
 mcs_status mcs_solve_batch_static(int32_t count, const mcs_graph *G, const mcs_graph *H,

@@ -13,7 +13,9 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)MCS_STATIC_SCRATCH_BYTES;
+// (2 KiB beyond the promised size: the launch's counters, one copy per XCD,
+// take one of them, which must not push a batch out that fits without)
+constexpr size_t kScratchBytes = (size_t)MCS_STATIC_SCRATCH_BYTES + 2048;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
