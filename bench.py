@@ -131,6 +131,19 @@ def kernel_for(word: int, tuning: dict):
     return "mcs_search.hip", "mcs_search_kernel"
 
 
+def lds_unit(source: str, word: int) -> str:
+    """What mcs_stats.lds_bytes counts for the kernel."""
+    if source == "mcs_lane.hip":
+        return ("algorithmic: each pushed frame's classes written once and read once per two "
+                "partners" + (", and the partners' rows" if word <= 8 else "") +
+                " (mcs_stats.lds_bytes, from the kernel's counters)")
+    return ("algorithmic: adjacency rows of v and the partners per child batch, "
+            "and each pushed frame's classes written once and read twice "
+            "(mcs_stats.lds_bytes, from the kernel's counters)"
+            + ("; with 128- and 256-bit rows the classes and v's G row live in "
+               "the workspace (L1/L2), not LDS" if word >= 16 else ""))
+
+
 def traffic_for(workload: str, source: str, nodes: float):
     """HBM bytes of a launch of `nodes` nodes, or None."""
     t = TRAFFIC.get(workload)
@@ -400,6 +413,8 @@ def main():
         "time_to_proof_s": _spread(t_proof),
         "busy_frac": sum(busy) / len(busy) if busy else 0.0,
         "active_lane_frac": lane_slots / (64.0 * batches) if batches else 0.0,
+        "active_lane_unit": "lanes with a search" if kernel_src == "mcs_lane.hip"
+                            else "lanes with a class",
         "children_per_batch": children / batches if batches else 0.0,
         "search_stats": {"steps_per_node": batches / nodes if nodes else 0.0,
                          "children_per_node": children / nodes if nodes else 0.0,
@@ -421,11 +436,7 @@ def main():
         "lds": {"achieved_GBps": lds_bytes / kern_s / 1e9 if kern_s else 0.0,
                 "peak_GBps": PEAK_LDS_BYTES / 1e9,
                 "frac": lds_bytes / kern_s / PEAK_LDS_BYTES if kern_s else 0.0,
-                "bytes": "algorithmic: adjacency rows of v and the partners per child batch, "
-                         "and each pushed frame's classes written once and read twice "
-                         "(mcs_stats.lds_bytes, from the kernel's counters)"
-                         + ("; with 128- and 256-bit rows the classes and v's G row live in "
-                            "the workspace (L1/L2), not LDS" if word >= 16 else "")},
+                "bytes": lds_unit(kernel_src, word)},
         "hbm": {"achieved_GBps": traffic * K / kern_s / 1e9 if traffic and kern_s else None,
                 "peak_GBps": PEAK_HBM_BYTES / 1e9,
                 "frac": traffic * K / kern_s / PEAK_HBM_BYTES if traffic and kern_s else None,

@@ -12,9 +12,10 @@
  * a child (v, w) splits every class by adjacency to v in G and to w in H, and
  * is pruned when |M| + sum over classes of min(|L|, |R|) cannot beat the
  * incumbent.  The library runs this on the GPU: many depth-first searches per
- * wavefront (one per segment of 16 or 8 lanes, a node's bitset classes
- * across the segment's lanes), a device work queue shared by all of them for
- * load balancing, and a per-instance incumbent updated with atomics.
+ * wavefront (one in every lane; or one per segment of 16, 8 or 4 lanes or one
+ * per wavefront, a node's bitset classes across the lanes), work shared inside
+ * the wavefront, the workgroup and through device queues, and a per-instance
+ * incumbent updated with atomics.
  *
  * Conventions for every entry point:
  *   - No exception crosses the ABI; every call returns an mcs_status.
@@ -225,10 +226,15 @@ typedef struct {
 /* Whole-launch statistics, filled by mcs_plan_stats. */
 typedef struct {
     int64_t nodes;             /* sum over instances */
-    int64_t batches;           /* child batches evaluated by all wavefronts */
+    int64_t batches;           /* child batches evaluated by all wavefronts
+                                  (a search in every lane: steps of the 64
+                                  searches) */
     int64_t children;          /* children evaluated (with re-evaluations) */
-    int64_t lane_slots;        /* lanes holding a class in those batches */
-    int64_t donations;         /* nodes published to the shared queue */
+    int64_t lane_slots;        /* lanes holding a class in those batches (a
+                                  search in every lane: lanes with a search
+                                  in those steps) */
+    int64_t donations;         /* nodes published to the shared queue, or given
+                                  to an idle lane or wavefront beside it */
     int64_t pops;              /* nodes taken from the shared queue */
     int32_t waves;             /* wavefronts launched */
     int32_t blocks;            /* workgroups launched */
@@ -239,16 +245,25 @@ typedef struct {
                                   of waves x kernel time went to looking for
                                   work (load imbalance and queue latency) */
     int64_t hbm_frames;        /* frames placed in the HBM part of a segmented
-                                  search's class stack */
-    int32_t stack_classes;     /* class-stack capacity per wavefront */
-    int32_t max_stack_used;    /* most classes any wavefront's stack held */
+                                  search's class stack (a search in every
+                                  lane: in the wavefront's worst-case area;
+                                  what its rings of LDS pass on to HBM is not
+                                  counted) */
+    int32_t stack_classes;     /* class-stack capacity per wavefront (or per
+                                  segment or lane) */
+    int32_t max_stack_used;    /* most classes (a search in every lane: with
+                                  frame headers) any search's stack held */
     double sleep_wave_s;       /* wavefront-seconds idle wavefronts spent in
                                   back-off sleeps (part of the time not busy) */
     int64_t lds_bytes;         /* algorithmic bytes through LDS: the adjacency
                                   rows each child batch reads (v's and its
                                   partners'), and the classes of each pushed
                                   frame, written once and read twice (headers
-                                  and mapping entries are not counted) */
+                                  and mapping entries are not counted); a
+                                  search in every lane: the classes of each
+                                  frame, written once and read once per two
+                                  partners, and up to 64 vertices the
+                                  partners' rows */
     int64_t node_classes;      /* classes split by the matched children counted
                                   in nodes, each counted once (siblings that a
                                   batch evaluates again after a descent are

@@ -1296,7 +1296,15 @@ mcs_status mcs_plan_stats(const mcs_plan *p, mcs_stats *st) {
     // its C partners (one word each, two when directed); each pushed frame's
     // classes (L and R words) are written once and read twice (at the descent
     // and when the search returns to the frame).
-    {
+    if (p->lane) {
+        // A search in every lane: two partners read a frame's classes
+        // together, a child's frame is written once (it stays in LDS unless
+        // deeper ones need the room), and up to 64 vertices the partners' rows
+        // are there too.
+        const int64_t entries = (int64_t)(p->h_stats.node_classes / 2 + p->h_stats.pushed_classes);
+        const int rw = p->word_bytes <= 8 ? (p->directed ? 2 : 1) * p->word_bytes : 0;
+        z.lds_bytes = entries * 2 * p->word_bytes + (int64_t)p->h_stats.children * rw;
+    } else {
         // (the segmented kernel reads both rows per child; "batches" are its steps)
         const int64_t rows = p->seg_log ? 2 * (int64_t)p->h_stats.children
                                         : (int64_t)p->h_stats.batches + (int64_t)p->h_stats.children;
