@@ -111,7 +111,8 @@ def kernel_hash(source: str) -> str:
     """code_hash of a kernel source file together with the device headers
     it includes."""
     text = ""
-    for name in (source, "mcs_device.h", "mcs_layout.h"):
+    names = (source, "mcs_device.h", "mcs_layout.h")
+    for name in names + (("mcs_team.h",) if source == "mcs_lane.hip" else ()):
         with open(os.path.join(ROOT, "paper_1908_06418_amd", "csrc", name)) as f:
             text += f.read() + "\n"
     return code_hash(text)

@@ -22,8 +22,8 @@
 // 35 vertices take 7 to 10 VALU instructions a node (28 with segments) and fill
 // 85 to 92% of the issue slots, 95% of the lanes holding a search; 43% of the
 // lane slots do work, since a loop over classes runs for the wavefront's
-// longest frame.  60 pairs of 30 vertices: 443 ms with segments, 93 here; 256
-// of 33: 601 and 150.  What is left of a small search is a chain of steps of
+// longest frame.  60 pairs of 30 vertices: 454 ms with segments, 96 here; 256
+// of 33: 541 and 113.  What is left of a small search is a chain of steps of
 // about 1 us: one pair of 16 vertices takes 3.6 ms with segments, 0.5 here.
 //
 // All lanes of a wavefront work on one instance, so its incumbent is a
@@ -51,7 +51,8 @@
 //
 // Work sharing, on three levels.  Idle lanes take whole frames from busy
 // lanes of their wavefront, all of them at once (steal()): the lowest open
-// frame of the lanes whose lowest open frame is shallowest.  A wavefront with
+// frame of the lanes where it is shallowest, or (undirected rows of up to 64
+// bits) of those whose top frame has the highest bound.  A wavefront with
 // no work raises its bit in the workgroup's LDS; a busy one that sees it
 // writes a frame straight into the idle one's stack (feed()).  Between
 // workgroups frames travel as records through the per-XCD rings of
@@ -77,7 +78,9 @@ constexpr int kReads = 4;
 // after so many steps (8 to 28 lanes: within 3%).
 constexpr int kIdleLanes = 12, kStealSteps = 8;
 // Frames may lie so much deeper than the shallowest open one to be taken, or
-// their lanes' bounds so much below the highest (steal()).
+// their lanes' bounds so much below the highest (steal()): with 0 too few
+// lanes are served (six pairs of 30 vertices one by one 53 ms); 2 to 5 take the
+// same time within 5%.
 constexpr int kStealSpan = 9, kStealBounds = 5;
 // A wavefront feeds waiting siblings once every kFeedSteps while it is rich
 // (so many lanes busy), and now and then anyway.  Feeding at every step cuts
@@ -578,7 +581,8 @@ struct LaneSearch {
     // (The network is evaluated for one vertex at a time, a hidden unit per
     // lane: some 10,000 instructions a frame, but only the shallow ones come
     // here, and all of their subtrees' frames take the lanes' own path: 24
-    // pairs of 28 vertices take 34 ms, and 152 with a search per wavefront.)
+    // pairs of 28 vertices take 35 ms, and 142 with a search per wavefront.
+    // Deeper orders go to that kernel, by the plan's rule.)
     __device__ __forceinline__ void consult(int l) {
         wave_sync();  // (entries and orders written by other lanes)
         const int fK = rl(K, l), fd = rl(d, l), fsel = rl(sel, l), fb = rl(base, l);
@@ -971,9 +975,11 @@ struct LaneSearch {
     // near the leaves is gone in a few steps.  Undirected rows of up to 64
     // bits: from the lanes whose top frame has (nearly) the highest bound,
     // which finds large mappings sooner (six pairs of 30 vertices one by one 45
-    // ms by depth and 38 by bound, 4,096 of 15 to 25 34 and 25, 4,096 of 10 to 35
-    // 11 to 16 s and 9 to 18; the other kinds of pairs were slower that
-    // way: 60 directed labelled pairs 4.0 and 4.5 ms, 254 vertices 55 and 67).
+    // ms by depth and 38 by bound, 4,096 of 15 to 25 34 and 25; the 4,096 of 10
+    // to 35, where a few very sparse pairs decide, show no difference beyond
+    // their spread: 11 to 18 s by depth, 9 to 21 by bound, eight launches each;
+    // the other kinds of pairs were slower that way: 60 directed labelled
+    // pairs 4.0 and 4.5 ms, 254 vertices 55 and 67).
     __device__ __forceinline__ void steal() {
         const bool is_i = t < 0;
         bool is_v = t >= 0 && lo_t < t;
