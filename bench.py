@@ -37,21 +37,21 @@ PEAK_LDS_BYTES = 256 * 128 * 2.4e9     # CUs x 128 bytes per clock x clock: LDS 
 PEAK_HBM_BYTES = 8e12
 
 # HBM bytes of one launch of the search kernel, from the copy-calibrated
-# FETCH_SIZE / WRITE_SIZE runs recorded in profiles/, and the nodes of those
-# launches (the parallel search order varies, and the node count with it);
-# reported, for the timed launches' nodes, only while the kernel code
-# (comments aside, code_hash) is the one those counters were taken on.
+# FETCH_SIZE / WRITE_SIZE runs recorded in profiles/: a part that every launch
+# moves and a part per node (the parallel search order varies, and the node
+# count with it); reported, for the timed launches' nodes, only while the
+# kernel code (comments aside, code_hash) is the one those counters were taken
+# on.
 TRAFFIC = {
-    # profiles/mcs_lane_kernel_c4.md: FETCH_SIZE 5,431,731,007 KiB x 1.9997 in a
-    # launch of 4.692e11 nodes, WRITE_SIZE 9,718,904,245 KiB x 1.000 in one of
-    # 4.539e11
-    "c4": {"source": "mcs_lane.hip", "kernel_code_hash": "b34718448c5969a5",
-           "bytes": 21_074_674_000_000, "nodes": 461_531_919_000},
-    # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 35,698,831.4 KiB x 1.9997 in a
-    # launch of 4.999e8 nodes, WRITE_SIZE 46,421,048.1 KiB x 1.000 in one of
-    # 4.681e8
-    "w": {"source": "mcs_lane.hip", "kernel_code_hash": "b34718448c5969a5",
-          "bytes": 120_635_393_000, "nodes": 484_020_000},
+    # profiles/mcs_lane_kernel_c4.md: straight lines through five FETCH_SIZE and
+    # five WRITE_SIZE launches of 4.7e11 to 1.5e12 nodes, within 2% of each
+    "c4": {"source": "mcs_lane.hip", "kernel_code_hash": "7a20823632c33e99",
+           "bytes": 17.336e12, "per_node": 8.157},
+    # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 34,762,876.9 KiB x 1.9997 in a
+    # launch of 4.879e8 nodes, WRITE_SIZE 48,466,074.4 KiB x 1.000 in one of
+    # 4.886e8
+    "w": {"source": "mcs_lane.hip", "kernel_code_hash": "7a20823632c33e99",
+          "bytes": 0.0, "per_node": 247.5},
 }
 
 # Algorithmic 32-bit lane operations of one matched child (v, w), per class
@@ -121,7 +121,7 @@ def kernel_hash(source: str) -> str:
 def kernel_for(word: int, tuning: dict):
     """Source and name of the kernel that serves rows of `word` bytes under
     these knobs (the library's rule; no workload here has wide pairs whose
-    root bound is near their size)."""
+    root bound is near their size, or is one of near copies)."""
     seg_lanes = int(tuning.get("seg_lanes", 0) or 0)
     knob = lambda k: int(tuning.get(k, 0) or 0)  # noqa: E731
     if seg_lanes == 0 and knob("stack_classes") <= 0 and not knob("single_wave") and \
@@ -150,7 +150,7 @@ def traffic_for(workload: str, source: str, nodes: float):
     t = TRAFFIC.get(workload)
     if not t or t.get("source") != source or t["kernel_code_hash"] != kernel_hash(source):
         return None
-    return t["bytes"] / t["nodes"] * nodes
+    return t["bytes"] + t["per_node"] * nodes
 
 
 def expected_sizes(fname):

@@ -71,7 +71,7 @@ class _Marshal:
 
     All row words of the batch go into one buffer, the labels into another:
     a numpy array, its ctypes pointers and a Python loop over the rows of each
-    graph took 72 ms for 4,096 pairs of 15 to 25 vertices, this and the
+    graph took 72 ms for 4,096 pairs of 10 to 22 vertices, this and the
     plan's creation take 12.  Graphs that the flat form does not take as they
     are (more vertices than the library allows, rows with bits above their
     words, entries that are no integers, labels that may be gone through only

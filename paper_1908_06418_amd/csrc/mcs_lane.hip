@@ -975,7 +975,7 @@ struct LaneSearch {
     // near the leaves is gone in a few steps.  Undirected rows of up to 64
     // bits: from the lanes whose top frame has (nearly) the highest bound,
     // which finds large mappings sooner (six pairs of 30 vertices one by one 45
-    // ms by depth and 38 by bound, 4,096 of 15 to 25 34 and 25; the 4,096 of 10
+    // ms by depth and 38 by bound, 4,096 of 10 to 22 34 and 25; the 4,096 of 10
     // to 35, where a few very sparse pairs decide, show no difference beyond
     // their spread: 11 to 18 s by depth, 9 to 21 by bound, eight launches each;
     // the other kinds of pairs were slower that way: 60 directed labelled
