@@ -49,9 +49,9 @@ TRAFFIC = {
            "bytes": 17.336e12, "per_node": 8.157},
     # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 34,762,876.9 KiB x 1.9997 in a
     # launch of 4.879e8 nodes, WRITE_SIZE 48,466,074.4 KiB x 1.000 in one of
-    # 4.886e8
+    # 4.886e8; launches differ by a few percent in nodes
     "w": {"source": "mcs_lane.hip", "kernel_code_hash": "7a20823632c33e99",
-          "bytes": 0.0, "per_node": 247.5},
+          "bytes": 120.8e9, "per_node": 0.0},
 }
 
 # Algorithmic 32-bit lane operations of one matched child (v, w), per class
