@@ -732,7 +732,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     // stack's LDS part that leaves to each segmented search.
     auto wave_share = [&](int wpc) {
         const int blocks_cu = std::max(1, (wpc + 3) / 4);
-        return ((lds_cu / blocks_cu) / kLdsGranule * kLdsGranule - 256) / 4;
+        return ((lds_cu / blocks_cu) / kLdsGranule * kLdsGranule - mcs::kParamLds) / 4;
     };
     auto seg_cap_at = [&](int wpc) {
         const int room = wave_share(wpc) / nseg - per_wave(0) / nseg - 16;
@@ -780,7 +780,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
     const int lane_rows = p->word_bytes <= 8
                               ? mcs::align16((directed ? 4 : 2) * p->arows * p->word_bytes)
                               : 0;
-    const int static_lds = p->lane ? mcs::kLaneTeamBytes : 256;
+    const int static_lds = p->lane ? mcs::kLaneTeamBytes : mcs::kParamLds;
     const int want_waves =
         p->tun.waves_per_cu > 0 ? p->tun.waves_per_cu * cus
         : p->lane    ? lane_wpc * cus
@@ -993,8 +993,20 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.cap_classes = p->cap_classes;
     sp.frames = p->frames;
     sp.lds_per_wave = p->lds_per_wave;
-    int cm = p->tun.children_per_wave;
-    sp.cmax = (cm == 1 || cm == 2 || cm == 4 || cm == 8) ? cm : 8;
+    if (p->lane) {
+        sp.lane_rc = p->lane_rc;
+        sp.lane_stride = p->lane_stride;
+        sp.lane_map_bytes = p->lane_map;
+        sp.lane_big = p->lane_big;
+        sp.check_ticks = p->tun.check_interval > 0 ? 0 : (int)(p->tick_hz * 10e-6);
+    } else {
+        const int cm = p->tun.children_per_wave;
+        sp.cmax = (cm == 1 || cm == 2 || cm == 4 || cm == 8) ? cm : 8;
+        sp.single_wave = p->tun.single_wave ? 1 : 0;
+        sp.seg_log = p->seg_log;
+        sp.seg_bytes = p->seg_bytes;
+        sp.lane_rc = 0;
+    }
     sp.donate_low = p->tun.donate_low > 0 ? p->tun.donate_low
                                           : (p->tun.donate_low < 0 ? -1 : 2);
     // Any frame may be handed out by default: a depth cut-off left the last
@@ -1007,7 +1019,6 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
                                               : 128;
     sp.reprune = p->tun.no_reprune ? 0 : 1;
     sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : p->lane ? 16 : 32;
-    sp.single_wave = p->tun.single_wave ? 1 : 0;
     sp.policy = p->policy;
     sp.policy_depth = p->policy_depth;
     sp.policy_levels = p->policy_levels;
@@ -1019,14 +1030,7 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.dead_rel = p->dead_rel;
     sp.hstack = p->hstack_stride ? p->ws + p->off_hstack : nullptr;
     sp.hstack_stride = p->hstack_stride;
-    sp.seg_log = p->seg_log;
-    sp.seg_bytes = p->seg_bytes;
     sp.arows = p->arows;
-    sp.lane_rc = p->lane_rc;
-    sp.lane_stride = p->lane_stride;
-    sp.lane_map_bytes = p->lane_map;
-    sp.lane_big = p->lane_big;
-    sp.check_ticks = p->tun.check_interval > 0 ? 0 : (int)(p->tick_hz * 10e-6);
 
     mcs::ResetParams &rp = p->rp;
     rp.inst = sp.inst;

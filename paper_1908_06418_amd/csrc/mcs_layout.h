@@ -107,13 +107,20 @@ struct SearchParams {
     int cap_classes;      // LDS class capacity of one wavefront's stack
     int frames;           // frame headers per wavefront (largest min(nG, nH) + 1)
     int lds_per_wave;     // bytes
-    int cmax;             // children per batch (1, 2, 4, 8)
+    union {
+        int cmax;         // children per batch (1, 2, 4, 8)
+        int lane_big;     // lane kernel: entries of a wavefront's worst-case area
+    };
     int donate_low;       // records a busy wavefront keeps queued in its XCD's ring (< 0: never donate)
     int donate_depth;     // only frames with |M| <= this are donated
     int check_interval;
     int backoff_max;      // most sleeps (of about 3.4 us) between an idle wavefront's polls
     int reprune;
-    int single_wave;
+    union {
+        int single_wave;
+        int check_ticks;  // lane kernel: a workgroup looks at what all XCDs share
+                          // once in so many realtime ticks
+    };
     const uint16_t *policy;  // half-precision policy parameters, or null
     int policy_depth;        // policy orders frames with |M| <= this
     int policy_mode;         // bit 0: policy picks v; bit 1: policy orders partners
@@ -129,17 +136,23 @@ struct SearchParams {
                                      // (128-bit rows), [waves][searches][hstack_stride]
                                      // (segments: the part above the LDS part)
     long long hstack_stride;         // bytes per stack (0: no HBM part)
-    int seg_log;                     // segmented kernel: 2^seg_log lanes per search (0: one
+    union {
+        int seg_log;                 // segmented kernel: 2^seg_log lanes per search (0: one
                                      // search per wavefront)
-    int seg_bytes;                   // segmented kernel: LDS bytes per search (seg_layout)
-    int arows;                       // segmented kernel: adjacency rows kept per graph in LDS
+        int lane_stride;             // lane kernel: bytes of one lane's stack in HBM
+    };
+    union {
+        int seg_bytes;               // segmented kernel: LDS bytes per search (seg_layout)
+        int lane_map_bytes;          // lane kernel: bytes of the mapping, the first of a lane's
+    };
+    int arows;                       // segmented and lane kernels: adjacency rows kept per graph
     int lane_rc;                     // lane kernel: stack entries of a lane in LDS (a ring)
-    int lane_stride;                 // lane kernel: bytes of one lane's stack in HBM
-    int lane_map_bytes;              // ... of which the mapping takes the first
-    int lane_big;                    // lane kernel: entries of a wavefront's worst-case area
-    int check_ticks;                 // lane kernel: a workgroup looks at what all XCDs share
-                                     // once in so many realtime ticks
 };
+// The kernels with segments and with a search per wavefront keep a copy of the
+// parameters in LDS, beside the wavefronts' parts; what only the lane kernel
+// needs lies where they keep what it does not.
+constexpr int kParamLds = 256;
+static_assert(sizeof(SearchParams) <= kParamLds, "the host leaves room for it in LDS");
 
 struct ResetParams {
     const DevInst *inst;

@@ -34,3 +34,8 @@ def test_transitions_of_a_team(tmp_path):
 def test_records_that_are_taken_fit(tmp_path):
     code, out = _run(tmp_path, "record")
     assert code == 0, out
+
+
+def test_launch_parameters_fit_their_place_in_lds(tmp_path):
+    code, out = _run(tmp_path, "params")
+    assert code == 0, out
