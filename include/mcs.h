@@ -99,9 +99,10 @@ typedef struct {
                                   paper delegates only above PART_LEVEL
                                   (0: any depth -- the largest min(nG, nH)) */
     int32_t check_interval;    /* search steps between queue/limit checks (0: 128;
-                                  with a search in every lane 4, and the
-                                  queue and the limits at most once per
-                                  10 us and workgroup) */
+                                  with a search in every lane 4, or 1 under
+                                  a node limit below 2,048 per wavefront, and
+                                  the queue and the time limit at most once
+                                  per 10 us and workgroup) */
     int32_t no_reprune;        /* 1: do not re-test a frame's bound against the
                                   incumbent when the search returns to it */
     int32_t single_wave;       /* 1: one search alone (the first segment of one

@@ -91,7 +91,8 @@ constexpr int kFeedSteps = 4, kFeedRich = 48, kFeedAnyway = 64;
 constexpr unsigned kFedGap = 16;
 
 // With a node limit or a dead-end forecast a wavefront hands its nodes in after
-// so many, or so many steps.  Handed in at every check, every four steps, a
+// so many (fewer for small ones: held_back()), or so many steps.  Handed in at
+// every check, every four steps, a
 // limit that is never met cost 60 pairs of 30 vertices 98 ms instead of 82 and a
 // forecast 166; so they take 83 and 85.
 constexpr int kFlushNodes = 1000;
@@ -196,10 +197,11 @@ struct LaneSearch {
     bool stop, roots_left;
     int my_ring, steal_from, other, since_check;
     unsigned flushed;    // the step of the last flush
+    int flush_at;        // nodes that make the next one
     u64w t_start, n_steps, n_lanes, n_don, n_pops, n_busy, n_sleep, n_big;
     u64w n_child, n_ncls, n_pushed;
 
-    __device__ LaneSearch(const KernArgs &p, Team &tm, lds_ptr<char> lds, int wave_in_block,
+    __device__ __forceinline__ LaneSearch(const KernArgs &p, Team &tm, lds_ptr<char> lds, int wave_in_block,
                           long long wave)
         : P(p), T(tm) {
         lane = lane_id();
@@ -233,6 +235,7 @@ struct LaneSearch {
         steal_from = other = my_ring;
         since_check = 0;
         flushed = 0;
+        flush_at = held_back();
         t_start = n_steps = n_lanes = n_don = n_pops = n_busy = n_sleep = n_big = 0;
         n_child = n_ncls = n_pushed = 0;
     }
@@ -1511,21 +1514,46 @@ struct LaneSearch {
         c_child = c_unm = c_ncls = c_pushed = 0;
         return sum;
     }
-    // (lane 0) Nodes to the instance's count.
-    __device__ __forceinline__ void add_nodes(u64w n) {
+    // (lane 0) Nodes to the instance's count; true: the limit has been passed
+    // (whoever passes it tells the others).
+    __device__ __forceinline__ bool add_nodes(u64w n) {
         if (n == 0)
-            return;
+            return false;
         a_add64(&P.nodes[inst], n);
-        if (P.node_limit > 0) {
-            const u64w tot = a_add64(&P.g->node_total, n) + n;
-            if ((long long)tot > P.node_limit)
-                raise_flag(kFlagStop);
-        }
+        if (P.node_limit <= 0)
+            return false;
+        const u64w before = a_add64(&P.g->node_total, n), limit = (u64w)P.node_limit;
+        if (before <= limit && before + n > limit)
+            raise_flag(kFlagStop);
+        return before + n > limit;
     }
     __device__ __forceinline__ void flush_nodes() {
         const u64w n = count_nodes();
+        int over = 0;
         if (lane == 0)
-            add_nodes(n);
+            over = add_nodes(n) ? 1 : 0;
+        if (rl(over, 0))
+            stop = true;
+    }
+    __device__ __forceinline__ long long launched() const {
+        return (long long)gridDim.x * (blockDim.x >> 6);
+    }
+    // Nodes that a wavefront may hold back: over all wavefronts a sixteenth of
+    // the limit, a quarter of what a forecast waits for.
+    __device__ __forceinline__ int held_back() const {
+        const long long all = launched();
+        int x = kFlushNodes;
+        while (x > 1 && ((P.node_limit > 0 && 16 * all * x > P.node_limit) ||
+                         (P.dead_abs > 0 && 4 * all * x > P.dead_abs)))
+            x >>= 1;
+        return x;
+    }
+    // Steps between checks.  Up to 128 children are evaluated in one: a limit of
+    // no more than a few of them per wavefront is looked at after each (unless
+    // check_interval was set: check_ticks is 0 then).
+    __device__ __forceinline__ int check_every() const {
+        const bool near = P.check_ticks != 0 && P.node_limit > 0 && P.node_limit < 2048 * launched();
+        return near ? 1 : sc(P.check_interval);
     }
     DEV u64w lanes_total(uint32_t x) {
         // (16-bit pieces: 64 of them sum below 2^31)
@@ -1586,7 +1614,7 @@ struct LaneSearch {
         }
         if (P.node_limit > 0 || P.dead_abs > 0) {
             if ((unsigned)n_steps - flushed >= kFlushSteps ||
-                wave_sum((int)(c_child + c_unm)) >= kFlushNodes) {
+                wave_sum((int)(c_child + c_unm)) >= flush_at) {
                 flushed = (unsigned)n_steps;
                 flush_nodes();
                 if (P.dead_abs > 0)
@@ -1734,7 +1762,7 @@ struct LaneSearch {
 
     __device__ __forceinline__ void main_loop() {
         t_start = now_ticks();
-        const int check_interval = sc(P.check_interval);
+        const int check_interval = check_every();
         int since_steal = 0, since_feed = 0;
         u64w t_busy0 = t_start;
         // the first instances go to the first wavefronts of all workgroups

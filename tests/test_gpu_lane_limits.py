@@ -45,3 +45,22 @@ def test_a_node_limit_stops_soon_after(gpu, limit):
         plan.close()
     assert st.stopped == 1 and not any(r.optimal for r in res)
     assert limit <= sum(r.nodes for r in res) == st.nodes <= limit + 8000 * st.waves
+
+
+@pytest.mark.parametrize("limit", [1000, 20_000, 200_000, 2_000_000])
+@pytest.mark.parametrize("seeds", [1, 10])
+def test_small_node_limits_are_met_closely(gpu, limit, seeds):
+    """A small limit is looked at after every step, with next to nothing held
+    back: what comes on top is the step that each wavefront is in, and while
+    a search spreads, its lanes double at most from one step to the next (so
+    twice the limit, and again what starts before the stop is seen)."""
+    from paper_1908_06418_amd import Plan
+    pairs = mi.pairs_c2(ns=(35,), ps=(0.3, 0.5), seeds=range(seeds))
+    print(f"lane limits, {len(pairs)} pairs, {limit} nodes", flush=True)
+    plan = Plan(pairs, node_limit=limit, time_limit_s=60).upload()
+    try:
+        plan.run()
+        st = plan.stats() if plan.results() else None
+    finally:
+        plan.close()
+    assert st.stopped == 1 and limit <= st.nodes <= 4 * limit + 1000
