@@ -99,10 +99,13 @@ typedef struct {
                                   paper delegates only above PART_LEVEL
                                   (0: any depth -- the largest min(nG, nH)) */
     int32_t check_interval;    /* search steps between queue/limit checks (0: 128;
-                                  with a search in every lane 4, or 1 under
-                                  a node limit below 2,048 per wavefront, and
-                                  the queue and the time limit at most once
-                                  per 10 us and workgroup) */
+                                  with a search in every lane a step of the
+                                  64 searches counts as 32, each is looked
+                                  at under a node limit below 2,048 per
+                                  wavefront, and the queue and the time
+                                  limit at most once per 10 us and
+                                  workgroup, or that share of it which the
+                                  interval is of 128) */
     int32_t no_reprune;        /* 1: do not re-test a frame's bound against the
                                   incumbent when the search returns to it */
     int32_t single_wave;       /* 1: one search alone (the first segment of one

@@ -993,18 +993,27 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     sp.cap_classes = p->cap_classes;
     sp.frames = p->frames;
     sp.lds_per_wave = p->lds_per_wave;
+    // (at most 2^16: the kernel's per-check step counters are 32-bit)
+    const int check = p->tun.check_interval > 0 ? std::min(p->tun.check_interval, 65536) : 128;
     if (p->lane) {
+        // A step of 64 searches does the work of some 32 of a segment's or a
+        // wavefront's.  Counted alike, check_interval 32 left the frames of
+        // wide pairs with one wavefront for too long: one directed labelled
+        // pair of 70 to 80 vertices took 24 ms (10 with a search per
+        // wavefront) and takes 8.9, eight 12.9 (8.0) and 6.1.
+        sp.check_interval = std::max(1, check / 32);
+        sp.check_ticks = (int)(p->tick_hz * 10e-6 * std::min(check, 128) / 128);
         sp.lane_rc = p->lane_rc;
         sp.lane_stride = p->lane_stride;
         sp.lane_map_bytes = p->lane_map;
         sp.lane_big = p->lane_big;
-        sp.check_ticks = p->tun.check_interval > 0 ? 0 : (int)(p->tick_hz * 10e-6);
     } else {
         const int cm = p->tun.children_per_wave;
         sp.cmax = (cm == 1 || cm == 2 || cm == 4 || cm == 8) ? cm : 8;
         sp.single_wave = p->tun.single_wave ? 1 : 0;
         sp.seg_log = p->seg_log;
         sp.seg_bytes = p->seg_bytes;
+        sp.check_interval = check;
         sp.lane_rc = 0;
     }
     sp.donate_low = p->tun.donate_low > 0 ? p->tun.donate_low
@@ -1013,10 +1022,6 @@ mcs_status mcs_plan_upload(mcs_plan *p, void *workspace, size_t bytes, void *str
     // hard instance's deep subtrees to one search while the rest idled
     // (measured on the batched workload: 27-28 s instead of 30-37 s).
     sp.donate_depth = p->tun.donate_depth > 0 ? p->tun.donate_depth : std::max(1, p->mmax);
-    // (at most 2^16: the kernel's per-check step counters are 32-bit)
-    sp.check_interval = p->tun.check_interval > 0 ? std::min(p->tun.check_interval, 65536)
-                        : p->lane             ? 4
-                                              : 128;
     sp.reprune = p->tun.no_reprune ? 0 : 1;
     sp.backoff_max = p->tun.backoff_max > 0 ? std::min(p->tun.backoff_max, 1024) : p->lane ? 16 : 32;
     sp.policy = p->policy;

@@ -1549,10 +1549,9 @@ struct LaneSearch {
         return x;
     }
     // Steps between checks.  Up to 128 children are evaluated in one: a limit of
-    // no more than a few of them per wavefront is looked at after each (unless
-    // check_interval was set: check_ticks is 0 then).
+    // no more than a few of them per wavefront is looked at after each.
     __device__ __forceinline__ int check_every() const {
-        const bool near = P.check_ticks != 0 && P.node_limit > 0 && P.node_limit < 2048 * launched();
+        const bool near = P.node_limit > 0 && P.node_limit < 2048 * launched();
         return near ? 1 : sc(P.check_interval);
     }
     DEV u64w lanes_total(uint32_t x) {
