@@ -97,7 +97,9 @@ typedef struct {
                                   open node (0: 2; < 0: never donate) */
     int32_t donate_depth;      /* only nodes with |M| <= this are donated, as the
                                   paper delegates only above PART_LEVEL
-                                  (0: any depth -- the largest min(nG, nH)) */
+                                  (0: any depth -- the largest min(nG, nH));
+                                  what a search in every lane hands on inside
+                                  a workgroup is not donated */
     int32_t check_interval;    /* search steps between queue/limit checks (0: 128;
                                   with a search in every lane a step of the
                                   64 searches counts as 32, each is looked

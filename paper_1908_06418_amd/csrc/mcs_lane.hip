@@ -1122,15 +1122,15 @@ struct LaneSearch {
         stop = true;  // (this wavefront leaves at the end of the step)
     }
 
-    // The lane with the shallowest open frame below its top gives it away:
-    // the lane (-1: none), the frame and its header, as scalars.  The frame
-    // is not marked yet.
-    __device__ __forceinline__ int pick_frame(int &fb, Hdr &h) {
+    // The lane with the shallowest open frame below its top, of |M| at most
+    // deepest, gives it away: the lane (-1: none), the frame and its header, as
+    // scalars.  The frame is not marked yet.
+    __device__ __forceinline__ int pick_frame(int deepest, int &fb, Hdr &h) {
         for (int tries = 0; tries < 4; ++tries) {
             const bool c = t >= 0 && lo_t < t;
             const uint32_t key = wave_min(c ? ((uint32_t)(d - t + lo_t) << 8) | (uint32_t)lane
                                             : ~0u);
-            if (key == ~0u || (int)(key >> 8) > P.donate_depth)
+            if (key == ~0u || (int)(key >> 8) > deepest)
                 return -1;
             const int l = (int)(key & 63u);
             int ft = rl(lo_t, l);
@@ -1150,7 +1150,7 @@ struct LaneSearch {
                 lo_base = fb;
                 lo_t = ft;
             }
-            if (ft < lt && (int)(h.x >> 24) <= P.donate_depth)
+            if (ft < lt && (int)(h.x >> 24) <= deepest)
                 return l;
         }
         return -1;
@@ -1204,7 +1204,7 @@ struct LaneSearch {
     __device__ __forceinline__ bool donate(int to) {
         int fb = 0;
         Hdr h;
-        const int l = pick_frame(fb, h);
+        const int l = pick_frame(P.donate_depth, fb, h);
         if (l < 0)
             return false;
         u64w ticket;
@@ -1260,7 +1260,7 @@ struct LaneSearch {
         wave_sync();
         int fb = 0;
         Hdr h;
-        const int l = pick_frame(fb, h);
+        const int l = pick_frame(255, fb, h);
         if (l < 0)
             return;
         const int w = (int)ctz(hungry);
