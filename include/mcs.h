@@ -156,9 +156,10 @@ typedef struct {
                                   above 64 vertices if some pair's Eq. 1
                                   bound at the root is over 7/8 of its
                                   smaller graph; and to 8 (64 with a policy)
-                                  above 32 vertices if all pairs' bounds are
-                                  and their graphs have (nearly) the same
-                                  degrees; and to 64 with a policy deeper
+                                  if all pairs' bounds are and their graphs
+                                  have (nearly) the same degrees, and have
+                                  more than 32 vertices, labels or
+                                  directions; and to 64 with a policy deeper
                                   than 3 (it picks v), 4 (it orders w) or 2
                                   (both); mcs_solve_batch_static: 8.
                                   Rows of more than 64 bits and the learned

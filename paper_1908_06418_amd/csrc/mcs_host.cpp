@@ -669,16 +669,18 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         // if any instance's bound is (eight pairs of a graph of 129 to 254
         // vertices and its copy: 2.5 ms with a search per wavefront, 71 ms
         // with one per lane); random labelled pairs have bounds of about 0.5
-        // to 0.8 of their size and frames of ten to twenty classes.  64-bit
+        // to 0.8 of their size and frames of ten to twenty classes.  Narrower
         // rows: if all are near copies as well, since random unlabelled pairs
         // have that bound too and run 4 to 8 times as fast here (8 pairs of a
         // 64-vertex graph and its copy: 2.0 ms on segments, 4.8 with one per
         // lane; one edge of the copies changed 2.6 and 4.5; 40 vertices 1.2
         // and 1.9, two edges changed 2.0 and 8.1; two edgeless graphs 1.1 and
-        // 2.2).  Copies of up to 32 vertices are over sooner here (1.5 and
-        // 0.9).
+        // 2.2).  Of up to 32 vertices the undirected unlabelled ones are over
+        // as soon here or sooner (8 of 24 0.8 and 0.4, 64 of 32 2.1 and 1.6),
+        // those with labels or directed, whose frames have more classes, are
+        // not (one of 28 0.23 and 0.5, 8 of 24 0.27 and 0.5).
         bool deep = false;
-        if (p->word_bytes >= 8) {
+        {
             auto near = [&](int i) { return 8 * p->root_bound[i] > 7 * p->m[i]; };
             bool any = false, all = true;
             for (int i = 0; i < ndev; i++) {
@@ -687,7 +689,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
                 all = all && d;
             }
             for (int k = 0; !wide && all && k < count; k++)
-                all = like_copies(G[k], H[k]);
+                all = (p->word_bytes > 4 || directed || G[k].label) && like_copies(G[k], H[k]);
             deep = wide ? any : all;
         }
         // One search alone is a single lane there, 1.1 us a node against 0.65

@@ -19,9 +19,9 @@ def test_never_donating_is_not_for_one_search_in_every_lane(mcs_lib, pairs, seg)
         workspace_size(pairs, tuning={"donate_low": 1, "seg_lanes": seg})
 
 
-def _copies(n, p, count, directed=False):
+def _copies(n, p, count, directed=False, labels=0):
     rng = np.random.default_rng([n, directed])
-    gs = [mi.random_small(rng, n, p, directed) for _ in range(count)]
+    gs = [mi.random_small(rng, n, p, directed, labels) for _ in range(count)]
     return [(g, mi.permute(g, [int(x) for x in rng.permutation(n)])) for g in gs]
 
 
@@ -44,8 +44,9 @@ EMPTY = [(mi.er_graph(50, 0.0, 1), mi.er_graph(50, 0.0, 2))]
 @pytest.mark.parametrize("pairs,lane", [
     (_copies(64, 0.2, 2), False), (_copies(34, 0.2, 1), False), (_copies(40, 0.15, 2, True), False),
     ([_flipped(p) for p in _copies(48, 0.2, 3)], False), (EMPTY, False), (_copies(32, 0.2, 2), True),
+    (_copies(28, 0.2, 2, True), False), (_copies(20, 0.3, 2, False, 6), False),
     (_random(40, 2), True), (_random(64, 1), True), (_copies(40, 0.2, 2) + _random(40, 1), True)])
-def test_copies_of_more_than_32_vertices_are_not_for_one_search_in_every_lane(mcs_lib, pairs, lane):
+def test_copies_with_long_frames_are_not_for_one_search_in_every_lane(mcs_lib, pairs, lane):
     from paper_1908_06418_amd import workspace_size
     segments = workspace_size(pairs, tuning={"seg_lanes": 8})
     assert (workspace_size(pairs) != segments) is lane
