@@ -763,20 +763,25 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
             }
         }
     }
-    // A search in every lane: 4 to 16 wavefronts per CU (8 with wide rows, by
-    // their registers), one per 2^15 nodes that the batch may need.  A tree's
+    // A search in every lane: 4 to 16 wavefronts per CU (up to 8 with wide rows,
+    // by their registers), one per 2^15 nodes that the batch may need.  A tree's
     // size is taken from its root: unlabelled random pairs double about every
     // 1.25 vertices (1e4 nodes at 16, 5e5 at 22, 3e7 at 30), labelled ones
     // every 2.2 matches that Eq. 1 allows at the root.  More wavefronts than
     // that only cut the work up: one pair G(30, 0.3) takes 6 ms with 4 per CU
     // and 8 with 16, 60 directed labelled pairs of 40 to 60 vertices 4 and 6,
-    // but 60 pairs G(30, p) 205 and 100.
+    // but 60 pairs G(30, p) 205 and 100.  Wide pairs: 1, 2, 4 or 8, their trees
+    // doubling about every 2.8 matches (one pair of 90 to 128 vertices with
+    // 4e5 nodes 3.9 ms with 1 and 5.5 with 4, and 4.7 with a search per
+    // wavefront; one of 129 to 180 with 4e7 95 with 1 and 57 with 8).
     double lane_nodes = 0;
     for (int i = 0; p->lane && i < ndev; i++)
-        lane_nodes += std::exp2(p->K0[i] <= 1 ? 0.8 * p->m[i] : 0.45 * p->root_bound[i]);
-    int lane_wpc = 4;
+        lane_nodes += std::exp2(wide            ? 0.36 * p->root_bound[i]
+                                : p->K0[i] <= 1 ? 0.8 * p->m[i]
+                                                : 0.45 * p->root_bound[i]);
+    int lane_wpc = wide ? 1 : 4;
     while (lane_wpc < (wide ? 8 : 16) && lane_nodes > 32768.0 * lane_wpc * cus)
-        lane_wpc += 4;
+        lane_wpc += wide ? lane_wpc : 4;
     // (a workgroup of up to a CU's wavefronts: they share work through LDS)
     const int lane_wpb_max = p->word_bytes <= 8 ? 16 : 8;
     const int lane_rows = p->word_bytes <= 8
