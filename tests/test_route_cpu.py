@@ -67,3 +67,13 @@ def test_deep_learned_orders_are_not_for_one_search_in_every_lane(mcs_lib, mode,
             _opts(0, 0, tun, policy=aligned, policy_depth=depth, policy_mode=mode)[0])))
             for tun in (None, {"seg_lanes": 64})]
         assert (size[0] != size[1]) is (depth <= deepest)
+
+
+@pytest.mark.parametrize("waves", [0, 1, 2, 3])
+def test_few_wavefronts_fit_the_largest_workgroup(mcs_lib, waves):
+    """(Without a device the plan assumes workgroups of 64 KiB of LDS.)"""
+    from paper_1908_06418_amd import workspace_size
+    rng = np.random.default_rng(12)
+    for n, labels in ((70, 50), (129, 100), (254, 180)):
+        pairs = [tuple(mi.random_small(rng, n, 0.3, True, labels) for _ in range(2))]
+        assert workspace_size(pairs, tuning={"waves_per_cu": waves}) > 0
