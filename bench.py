@@ -43,15 +43,15 @@ PEAK_HBM_BYTES = 8e12
 # kernel code (comments aside, code_hash) is the one those counters were taken
 # on.
 TRAFFIC = {
-    # profiles/mcs_lane_kernel_c4.md: straight lines through five FETCH_SIZE and
-    # five WRITE_SIZE launches of 4.7e11 to 1.5e12 nodes, within 2% of each
-    "c4": {"source": "mcs_lane.hip", "kernel_code_hash": "7a20823632c33e99",
-           "bytes": 17.336e12, "per_node": 8.157},
-    # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 34,762,876.9 KiB x 1.9997 in a
-    # launch of 4.879e8 nodes, WRITE_SIZE 48,466,074.4 KiB x 1.000 in one of
-    # 4.886e8; launches differ by a few percent in nodes
-    "w": {"source": "mcs_lane.hip", "kernel_code_hash": "7a20823632c33e99",
-          "bytes": 120.8e9, "per_node": 0.0},
+    # profiles/mcs_lane_kernel_c4.md: straight lines through four FETCH_SIZE and
+    # four WRITE_SIZE launches of 4.7e11 to 1.4e12 nodes, within 1% of each
+    "c4": {"source": "mcs_lane.hip", "kernel_code_hash": "b0e43a05373cd416",
+           "bytes": 17.376e12, "per_node": 8.064},
+    # profiles/mcs_lane_kernel_w.md: FETCH_SIZE 34,494,924.9 KiB x 1.9997 in a
+    # launch of 4.824e8 nodes, WRITE_SIZE 47,880,385.6 KiB x 1.000 in one of
+    # 4.839e8; launches differ by a few percent in nodes
+    "w": {"source": "mcs_lane.hip", "kernel_code_hash": "b0e43a05373cd416",
+          "bytes": 119.7e9, "per_node": 0.0},
 }
 
 # Algorithmic 32-bit lane operations of one matched child (v, w), per class
