@@ -698,7 +698,7 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         // of 24 vertices 6.5 s, and 3.1 on segments, eight to a wavefront; 24
         // directed labelled pairs of 70 to 90 2.7, and 0.7 with a search per
         // wavefront).  The learned policy goes with it (24 pairs of 28
-        // vertices, depth 1: 142 ms with a search per wavefront and 35 with
+        // vertices, depth 1: 147 ms with a search per wavefront and 32 with
         // one per lane) down to the depth where most of the time goes to the
         // scores, which a wavefront computes for one lane at a time there: 12
         // pairs of 26 vertices 78 and 51 ms at depth 3, 104 and 101 at 4, 124

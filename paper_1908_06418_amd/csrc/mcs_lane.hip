@@ -22,8 +22,8 @@
 // 35 vertices take 7 to 10 VALU instructions a node (28 with segments) and fill
 // 85 to 92% of the issue slots, 95% of the lanes holding a search; 43% of the
 // lane slots do work, since a loop over classes runs for the wavefront's
-// longest frame.  60 pairs of 30 vertices: 454 ms with segments, 96 here; 256
-// of 33: 541 and 113.  What is left of a small search is a chain of steps of
+// longest frame.  60 pairs of 30 vertices: 425 ms with segments, 86 here; 256
+// of 10 to 33: 636 and 166.  What is left of a small search is a chain of steps of
 // about 1 us: one pair of 16 vertices takes 3.6 ms with segments, 0.5 here.
 //
 // All lanes of a wavefront work on one instance, so its incumbent is a
@@ -584,7 +584,7 @@ struct LaneSearch {
     // (The network is evaluated for one vertex at a time, a hidden unit per
     // lane: some 10,000 instructions a frame, but only the shallow ones come
     // here, and all of their subtrees' frames take the lanes' own path: 24
-    // pairs of 28 vertices take 35 ms, and 142 with a search per wavefront.
+    // pairs of 28 vertices take 32 ms, and 147 with a search per wavefront.
     // Deeper orders go to that kernel, by the plan's rule.)
     __device__ __forceinline__ void consult(int l) {
         wave_sync();  // (entries and orders written by other lanes)
