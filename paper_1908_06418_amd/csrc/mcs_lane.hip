@@ -979,9 +979,9 @@ struct LaneSearch {
     // bits: from the lanes whose top frame has (nearly) the highest bound,
     // which finds large mappings sooner (six pairs of 30 vertices one by one 45
     // ms by depth and 38 by bound, 4,096 of 10 to 22 34 and 25; the 4,096 of 10
-    // to 35, where a few very sparse pairs decide, show no difference beyond
-    // their spread: 11 to 18 s by depth, 9 to 21 by bound, eight launches each;
-    // the other kinds of pairs were slower that way: 60 directed labelled
+    // to 35, where a few very sparse pairs decide, show little beyond their
+    // spread: 11.2 to 19.8 s by depth, mean 14.8 of 28 launches, 8.9 to 21.9 by
+    // bound, mean 14.0 of 42; the other kinds of pairs were slower that way: 60 directed labelled
     // pairs 4.0 and 4.5 ms, 254 vertices 55 and 67).
     __device__ __forceinline__ void steal() {
         const bool is_i = t < 0;
