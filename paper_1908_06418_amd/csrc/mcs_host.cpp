@@ -803,8 +803,10 @@ static mcs_status plan_create(int32_t count, const mcs_graph *G, const mcs_graph
         const int wpc = std::min(16, target_wpc);
         const int per_cu_blocks = (wpc + lane_wpb_max - 1) / lane_wpb_max;
         const int wpb = (wpc + per_cu_blocks - 1) / per_cu_blocks;
-        const int block = std::min(lds_cu / per_cu_blocks / kLdsGranule * kLdsGranule, max_lds_block);
-        const int share = (block - static_lds) / wpb;
+        // (a wavefront's part fits a workgroup; whether wpb of them do is seen below)
+        const int share =
+            std::min((lds_cu / per_cu_blocks / kLdsGranule * kLdsGranule - static_lds) / wpb,
+                     max_lds_block - static_lds);
         p->lane_rc = std::max(hdr_e + 2, std::min({worst_e, 250, (share - lane_rows) / (64 * entry)}));
         p->waves_per_block = wpb;
         const int want = p->word_bytes <= 4    ? 128
